@@ -19,13 +19,8 @@ constexpr int kEncTile = kEncThreads * kEncSymsPerThread;  // symbols per tile
 #ifndef QLC_DEC_THREADS_LOG2
 #define QLC_DEC_THREADS_LOG2 8
 #endif
-#ifndef QLC_DEC_STAGE_GROUPS
-#define QLC_DEC_STAGE_GROUPS 16
-#endif
 constexpr int kDecThreadsLog2 = QLC_DEC_THREADS_LOG2;
 constexpr int kDecThreads = 1 << kDecThreadsLog2;  // decode workgroup: one lane per chunk
-constexpr int kStageGroups = QLC_DEC_STAGE_GROUPS;  // decoded groups staged per lane (8 or 16)
-static_assert(kStageGroups == 8 || kStageGroups == 16, "stage depth");
 constexpr int kNumXcd = 8;  // MI355X: 8 accelerator complex dies
 // Layout modes: 0..3, SEARCH_DISTINCT_k = 16 + k for k = 1..8, SEARCH_AREAS4 = 32,
 // and the small alphabets 48..51 (16 or 64 symbols).

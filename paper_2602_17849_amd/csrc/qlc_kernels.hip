@@ -591,6 +591,8 @@ struct EncSmem {
 };
 
 // Encoder LUT entry of a table's (len << 11) | code word: code | len << 16.
+typedef uint32_t v2u32 __attribute__((ext_vector_type(2)));
+typedef uint32_t v3u32 __attribute__((ext_vector_type(3)));
 typedef uint32_t v4u32 __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ uint32_t enc_entry(uint32_t e) {
@@ -1022,97 +1024,142 @@ __global__ __launch_bounds__(kEncThreads) void k_encode(
 // LUT is re-indexed by the whole code word: because widths never decrease,
 // the codes of area a occupy the integer range [a << w_a, (a + 1) << w_a)
 // and these ranges are disjoint, so a 2048-entry LDS table maps code ->
-// symbol (bit 15 flags an invalid suffix; 32-bit entries, so gathered values
-// need no zero extension before packing).  The per-symbol chain is pure
+// symbol (16-bit entries: the top bit marks an invalid suffix).  The per-symbol chain is pure
 // VALU: the 3-bit area code selects the shift 29 - w_a from an 8-byte
 // register table (v_perm), the code is the window shifted right by it, and
 // three funnel shifts advance a 96-bit window by 3 + w_a bits.
 //
-// Memory: each lane streams its chunk in 32-byte superblocks (two 16-byte
-// bounds-checked buffer loads) into a private 4-superblock LDS ring (plus a
-// mirror of the first words, so a 4-word window never wraps), stored
-// word-major so that window reads never conflict on LDS banks.  A
-// superblock is requested three superblocks ahead of the window, at most
-// one per 8-symbol group; whole waves keep four register sets in rotation,
-// so a superblock is written to the ring four groups after its load was
-// issued (at least six groups before the window can reach it) and every
-// wave waits at fixed program points for loads that old.  Lanes that need
-// no superblock issue the loads with an out-of-range offset (zeros
-// returned, no memory touched).  Decoded bytes are staged per lane in LDS
-// and, every kStageGroups (16) groups, the wave stores its 64 lanes'
-// 128-byte output runs with coalesced stores (16 lanes per run, whole
-// 128-byte lines).
+// Memory: each lane's chunk arrives in 64-byte superblocks, loaded by four
+// lanes together, in a ring of four of them in LDS (Refill below); decoded
+// bytes change owner through LDS so that a wave stores its 64 lanes' output
+// in runs of 128 bytes (whole cache lines; 64-byte runs cost a quarter more).
+//
+// What bounds it: 256 MiB at C = 2048 are two waves on every SIMD.  A lone
+// wave decodes a group of 8 symbols in 610 cycles, its ~97 instructions at
+// 5-6 cycles each whatever they are; the pair takes about 450 per group and
+// wave.  With the loads and stores left out the kernel takes 110 us of its
+// 125: it is bound by its instruction stream, then by the memory system's
+// answer to 131,072 streams.  256 MiB 152 -> 125.5 us (4.0 TB/s of stream
+// and output); 48 shards of 1-32 MiB in one call 384 -> 315 us; one wave per
+// SIMD (32 Mi 6-bit symbols, C = 1024) 47.9 -> 46.5 us.
 // ===========================================================================
 constexpr int kDecLanes = kDecThreads;     // chunks per workgroup
-constexpr int kRingWords = 36;             // 4 x 8 ring words + 4 mirror words
-constexpr uint32_t kSbLog2Bits = 8;         // superblock: 256 bits = 32 bytes
-constexpr uint32_t kLookaheadBits = 768;   // request a superblock three ahead
-constexpr uint32_t kOobOffset = 0xFFFFFFC0u;
+constexpr uint32_t kSbLog2Bits = 9;        // superblock: 512 bits = 64 bytes
+constexpr uint32_t kSbBits = 1u << kSbLog2Bits;
+constexpr uint32_t kRingBits = 4 * kSbBits;  // ring of four superblocks
+constexpr int kRingWords = kRingBits / 32 + 3;  // ... and 3 mirror words
+constexpr uint32_t kLookaheadBits = 3 * kSbBits;  // request a superblock up to three ahead
+constexpr uint32_t kReach = 3 * 88 + 128;  // bits past q that four groups' windows may read
+static_assert(kReach + kSbBits <= kLookaheadBits, "a lane can always request what it may need");
+constexpr uint32_t kOobOffset = 0xFFFFF000u;  // (room for the offsets added to it)
 constexpr uint32_t kAreaSel = 0x01818180u;  // alignbit(kAreaSel, A, 29) = (A >> 29) | 0x0C0C0C00
+constexpr uint32_t kStagePairs = 8;        // pairs of 8-symbol groups per output run
+constexpr uint32_t kStageLanes = 16;       // output runs staged at a time
+constexpr uint32_t kStageRow = kStagePairs * 4 + 4;  // words of a staged run, padded: 16
+                                                     // runs start in 16 different quads of banks
 
+// The lanes' rings, then each wave's stage: the output runs of 16 lanes.
+constexpr uint32_t kStageWords = kStageLanes * kStageRow;  // per wave
+constexpr uint32_t kStageBase = kDecLanes * kRingWords;
 struct DecSmem {
-  uint32_t lut[2048];
-  uint32_t ring[kDecLanes * kRingWords];
-  uint2 stage[kDecLanes * kStageGroups];    // kStageGroups groups x 8 bytes per lane
+  uint16_t lut[2048];
+  __attribute__((aligned(16))) uint32_t ring[kStageBase + kDecLanes / 64 * kStageWords];
 };
-
-// Staging slot of group g of lane t: rotated by the lane so that the 8-byte
-// writes of a wave, and the reads of the coalesced flush, hit distinct LDS
-// banks.
-__device__ __forceinline__ uint32_t stage_slot(uint32_t g, uint32_t t) {
-  return kStageGroups == 8 ? ((g ^ (t >> 2)) & 7u) : ((g ^ (t >> 1)) & 15u);
-}
-
-struct Superblock {
-  uint4 q0, q1;
-};
+static_assert(sizeof(DecSmem) * 2 <= 160 * 1024, "two workgroups per CU");
 
 __device__ __forceinline__ uint4 bufload16(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);
 }
 
-__device__ __forceinline__ Superblock load_sb(__amdgpu_buffer_rsrc_t rsrc, uint32_t off) {
-  Superblock s;
-  s.q0 = bufload16(rsrc, off);
-  s.q1 = bufload16(rsrc, off + 16);
-  return s;
+// Lane r's value of each quad of lanes, in its four lanes.
+template <int r>
+__device__ __forceinline__ uint32_t quad_bcast(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, r * 0x55, 0xf, 0xf, true);
 }
 
-// Superblock `sb` (absolute number) into ring slot sb & 3 (words 8*(sb&3)),
-// in memory byte order (the window reads swap to most-significant-first);
-// slot 0's first four words are mirrored to words 32..35 so that a 4-word
-// window never wraps.
+// The four lanes of a quad load a superblock together, 16 bytes each: round
+// r (0..3) serves the quad's lane r.  A superblock per lane in pieces of 32
+// bytes of its own made every load instruction touch 64 cache lines and
+// fetch each 64-byte sector twice: that pattern alone (131,072 streams of
+// 1792 bytes read, 128-byte runs of 256 MiB written) takes 140 us on MI355X,
+// with four lanes per 64 bytes 91 us, and fully contiguous 85 us.
+//
 // The ring is stored word-major ("transposed"): word w of lane l sits at
-// ring[w * kDecLanes + l], so every lane only ever touches LDS bank l mod 64
+// ring[w * kDecLanes + l], so every lane only ever reads LDS bank l mod 64
 // and the window reads of a wave are free of bank conflicts whatever the
-// lanes' positions.
-__device__ __forceinline__ void ring_put(uint32_t* ring, uint32_t sb, const Superblock& s) {
-  uint32_t* r = ring + (sb & 3u) * 8u * kDecLanes;
-  const uint32_t v[8] = {s.q0.x, s.q0.y, s.q0.z, s.q0.w, s.q1.x, s.q1.y, s.q1.z, s.q1.w};
-#pragma unroll
-  for (int i = 0; i < 8; ++i) r[i * kDecLanes] = v[i];
-  if ((sb & 3u) == 0) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ring[(32 + i) * kDecLanes] = v[i];
-  }
-}
+// lanes' positions.  Words are byte-swapped to most-significant-first on
+// their way in.  Words 0..2 are mirrored behind the last slot, so that a
+// 4-word window never wraps.
+struct Refill {
+  uint4 data[4];       // by round: the piece this lane loads,
+  uint32_t at[4];      // and the ring word it goes to (~0: not requested)
 
+  template <int r>
+  __device__ __forceinline__ void issue1(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t word,
+                                         uint32_t lane) {
+    const uint32_t o = quad_bcast<r>(off) + (lane & 3u) * 16u;
+    const uint32_t w = quad_bcast<r>(word) + (lane & 3u) * 4u * kDecLanes;
+    at[r] = o < kOobOffset ? w : ~0u;
+    data[r] = bufload16(rsrc, o);
+  }
+  // off, word: this lane's request (stream byte, or kOobOffset for none; ring word)
+  __device__ __forceinline__ void issue(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, uint32_t word,
+                                        uint32_t lane) {
+    issue1<0>(rsrc, off, word, lane);
+    issue1<1>(rsrc, off, word, lane);
+    issue1<2>(rsrc, off, word, lane);
+    issue1<3>(rsrc, off, word, lane);
+  }
+  __device__ __forceinline__ void put(uint32_t* ring_all) const {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      if (at[r] != ~0u) {
+        const uint32_t v[4] = {__builtin_bswap32(data[r].x), __builtin_bswap32(data[r].y),
+                               __builtin_bswap32(data[r].z), __builtin_bswap32(data[r].w)};
+        uint32_t* d = ring_all + at[r];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) d[i * kDecLanes] = v[i];
+        if (at[r] < kDecLanes) {  // the first piece of slot 0
+#pragma unroll
+          for (int i = 0; i < 3; ++i) d[(kRingBits / 32 + i) * kDecLanes] = v[i];
+        }
+      }
+    }
+  }
+};
+
+// Position of a lane in its chunk's stream, relative to the wave's base (a
+// multiple of the ring's size, so that positions are also the ring's).
 struct DecLane {
-  uint32_t* ring;
-  uint64_t pm1;        // bit position of the next symbol, minus one
-  uint32_t sh_lo, sh_hi;
+  uint32_t q;          // bit of the next symbol, minus one
+  uint32_t F;          // first bit not requested yet (a multiple of kSbBits)
+  uint32_t have;       // first bit that is not in the ring yet
   uint32_t errbits;
+
+  // This lane's request: the superblock at F if it starts within the
+  // lookahead and before the chunk's end.
+  __device__ __forceinline__ void request(Refill& T, __amdgpu_buffer_rsrc_t rsrc, uint32_t endr,
+                                          uint32_t tid) {
+    const bool need = F < min(q + 1 + kLookaheadBits, endr);
+    T.issue(rsrc, need ? F >> 3 : kOobOffset, ((F & (kRingBits - 1)) >> 5) * kDecLanes + tid, tid);
+    F += need ? kSbBits : 0u;
+  }
+  // What was requested last, into the ring.
+  __device__ __forceinline__ void arrive(const Refill& T, uint32_t* ring_all) {
+    T.put(ring_all);
+    __builtin_amdgcn_wave_barrier();
+    have = F;
+  }
 };
 
 struct Window {
   uint32_t w0, w1, w2, w3;
 };
 
-// The four ring words holding bits pm1 + 1 .. pm1 + 96 (q = pm1, in the
-// ring's coordinates), as stored (memory byte order).
+// The four ring words of a lane's column holding bits q + 1 .. q + 96.
 __device__ __forceinline__ Window window_read(const uint32_t* ring, uint32_t q) {
-  const uint32_t* rr = ring + ((q >> 5) & 31u) * kDecLanes;
+  const uint32_t* rr = ring + ((q & (kRingBits - 1)) >> 5) * kDecLanes;
   Window w;
   w.w0 = rr[0];
   w.w1 = rr[kDecLanes];
@@ -1121,38 +1168,49 @@ __device__ __forceinline__ Window window_read(const uint32_t* ring, uint32_t q) 
   return w;
 }
 
-// The 8-symbol chain on a window read at q = pm1: e[k] receives the LUT
-// entries (gathers issued, not waited for); returns the bits consumed.
+// The 8-symbol chain on a window (most-significant-first words) read at q:
+// c[k] receives the code words; returns the bits consumed.  A wave issues one instruction about every five cycles
+// whatever the instruction (a lone wave's decode takes its instruction
+// count times that), so the chain does no work whose result cannot matter:
+// the area code comes from a plain shift (the bytes of `sft` above the
+// lowest are those of area 0, ignored by every shift and masked out of the
+// sum), and the 96-bit window A:B:C is only advanced as far as the remaining
+// codes (at most 11 bits each) can reach: C for the first two symbols, B for
+// the first five.
 __device__ __forceinline__ uint32_t decode_chain(const Window& W, uint32_t q, uint32_t sh_lo,
-                                                 uint32_t sh_hi, const uint32_t* __restrict__ lut,
-                                                 uint32_t (&e)[8]) {
-  const uint32_t w0 = __builtin_bswap32(W.w0), w1 = __builtin_bswap32(W.w1);
-  const uint32_t w2 = __builtin_bswap32(W.w2), w3 = __builtin_bswap32(W.w3);
+                                                 uint32_t sh_hi, uint32_t (&c)[8]) {
   const uint32_t sh0 = ~q;  // alignbit uses the low 5 bits: 32 - (pos & 31), or 0
-  uint32_t A = __builtin_amdgcn_alignbit(w0, w1, sh0);
-  uint32_t B = __builtin_amdgcn_alignbit(w1, w2, sh0);
-  uint32_t Cw = __builtin_amdgcn_alignbit(w2, w3, sh0);
+  uint32_t A = __builtin_amdgcn_alignbit(W.w0, W.w1, sh0);
+  uint32_t B = __builtin_amdgcn_alignbit(W.w1, W.w2, sh0);
+  uint32_t Cw = __builtin_amdgcn_alignbit(W.w2, W.w3, sh0);
   uint32_t ssum = 0;
 #pragma unroll
   for (int k = 0; k < 8; ++k) {
-    const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, A, 29);
-    const uint32_t sft = __builtin_amdgcn_perm(sh_hi, sh_lo, sel);  // 29 - width
-    e[k] = lut[A >> sft];
-    A = __builtin_amdgcn_alignbit(A, B, sft);
-    B = __builtin_amdgcn_alignbit(B, Cw, sft);
-    Cw = __builtin_amdgcn_alignbit(Cw, 0u, sft);
+    const uint32_t sft = __builtin_amdgcn_perm(sh_hi, sh_lo, A >> 29);  // 32 - length
+    c[k] = A >> (sft & 31u);
+    if (k < 7) A = __builtin_amdgcn_alignbit(A, k < 6 ? B : 0u, sft);
+    if (k < 5) B = __builtin_amdgcn_alignbit(B, k < 3 ? Cw : 0u, sft);
+    if (k < 2) Cw = __builtin_amdgcn_alignbit(Cw, 0u, sft);
     ssum += sft;
   }
-  return 256u - ssum;
+  return (0u - ssum) & 0xFFu;  // 256 - sum of (32 - length), at most 88
 }
+
+// LUT entry of an invalid suffix, and the invalid flags of a packed pair of
+// entries.
+constexpr uint32_t kBadEntry = 0x8000u;
+constexpr uint32_t kBadMask = kBadEntry | (kBadEntry << 16);
 
 // The 8 decoded bytes packed little-endian; the entries' invalid flags are
 // accumulated in errbits.
 __device__ __forceinline__ uint2 pack_group(const uint32_t (&e)[8], uint32_t& errbits) {
+  const uint32_t p0 = (e[1] << 16) | e[0], p1 = (e[3] << 16) | e[2];
+  const uint32_t p2 = (e[5] << 16) | e[4], p3 = (e[7] << 16) | e[6];
   uint2 r;
-  r.x = __builtin_amdgcn_perm(e[1], e[0], 0x0C0C0400u) | __builtin_amdgcn_perm(e[3], e[2], 0x04000C0Cu);
-  r.y = __builtin_amdgcn_perm(e[5], e[4], 0x0C0C0400u) | __builtin_amdgcn_perm(e[7], e[6], 0x04000C0Cu);
-  errbits |= e[0] | e[1] | e[2] | e[3] | e[4] | e[5] | e[6] | e[7];
+  r.x = __builtin_amdgcn_perm(p1, p0, 0x06040200u);
+  r.y = __builtin_amdgcn_perm(p3, p2, 0x06040200u);
+  errbits |= p0 | p1;
+  errbits |= p2 | p3;
   return r;
 }
 
@@ -1191,6 +1249,49 @@ __device__ __forceinline__ void store_group(QLC_GLOBAL uint8_t* p, uint2 v) {
   }
 }
 
+// Two consecutive groups (pack_group's words) in the output format: 16, 8 or
+// 12 bytes in the first words of a uint4.
+template <int kBits>
+__device__ __forceinline__ uint4 pack_pair(uint2 g0, uint2 g1) {
+  const uint2 a = pack_out<kBits>(g0), b = pack_out<kBits>(g1);
+  if (kBits == 8) return make_uint4(a.x, a.y, b.x, b.y);
+  if (kBits == 4) return make_uint4(a.x, b.x, 0u, 0u);
+  return make_uint4(a.x, (a.y & 0xFFFFu) | (b.x << 16), (b.x >> 16) | (b.y << 16), 0u);
+}
+
+// Store a pair's 2 * kBits bytes at byte off + soff (soff wave-uniform) of a
+// buffer resource.
+template <int kBits>
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                           uint32_t soff, uint4 v) {
+  if (kBits == 8) {
+    const v4u32 w = {v.x, v.y, v.z, v.w};
+    __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, off, soff, 0);
+  } else if (kBits == 4) {
+    const v2u32 w = {v.x, v.y};
+    __builtin_amdgcn_raw_buffer_store_b64(w, rsrc, off, soff, 0);
+  } else {
+    const v3u32 w = {v.x, v.y, v.z};
+    __builtin_amdgcn_raw_buffer_store_b96(w, rsrc, off, soff, 0);
+  }
+}
+
+// ... and only the first group's kBits bytes.
+template <int kBits>
+__device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                            uint32_t soff, uint4 v) {
+  if (kBits == 8) {
+    const v2u32 w = {v.x, v.y};
+    __builtin_amdgcn_raw_buffer_store_b64(w, rsrc, off, soff, 0);
+  } else if (kBits == 4) {
+    __builtin_amdgcn_raw_buffer_store_b32(v.x, rsrc, off, soff, 0);
+  } else {
+    __builtin_amdgcn_raw_buffer_store_b16((short)v.x, rsrc, off, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16((short)(v.x >> 16), rsrc, off + 2, soff, 0);
+    __builtin_amdgcn_raw_buffer_store_b16((short)v.y, rsrc, off + 4, soff, 0);
+  }
+}
+
 // Workgroup barrier that orders LDS accesses only: global loads in flight
 // stay in flight across it (__syncthreads() would wait for them).
 __device__ __forceinline__ void lds_barrier() {
@@ -1209,7 +1310,7 @@ __device__ __forceinline__ void table_to_lds(const qlc_table* __restrict__ t, ql
   if (tid < sizeof(qlc_table) / 16) ((uint4*)s)[tid] = ((const uint4*)t)[tid];
 }
 
-// Code -> symbol LUT of `table` into `lut` (2048 32-bit entries, bit 15 =
+// Code -> symbol LUT of `table` into `lut` (2048 16-bit entries, kBadEntry =
 // invalid suffix) and the shift table indexed by the window's top three
 // bits (byte i of sh_hi:sh_lo = 32 - prefix bits - width of the area the
 // top bits name).  A table whose areas 4..7 (or 2..7) are marked 0xFF has a
@@ -1246,7 +1347,7 @@ __device__ __forceinline__ AreaFields read_areas(const qlc_table* __restrict__ t
   return f;
 }
 
-__device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ table, uint32_t* lut,
+__device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ table, uint16_t* lut,
                               uint32_t& sh_lo, uint32_t& sh_hi) {
   sh_lo = 0;
   sh_hi = 0;
@@ -1276,7 +1377,7 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
   if (layered) {
     // Areas' code ranges are disjoint and every rank lies in one area, so
     // each rank's code is its own LUT entry: clear, then one write per rank.
-    for (uint32_t c = threadIdx.x; c < 2048; c += blockDim.x) lut[c] = 0x8000;
+    for (uint32_t c = threadIdx.x; c < 2048; c += blockDim.x) lut[c] = (uint16_t)kBadEntry;
     lds_barrier();
     for (uint32_t r = threadIdx.x; r < f; r += blockDim.x) {
       uint32_t a = 0;
@@ -1289,13 +1390,13 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
         oa = a == (uint32_t)k ? A.off[k] : oa;
       }
       const uint32_t suffix = r - oa;
-      if (suffix < (1u << wa)) lut[(a << wa) + suffix] = table->rank_to_sym[r];
+      if (suffix < (1u << wa)) lut[(a << wa) + suffix] = (uint16_t)table->rank_to_sym[r];
     }
   } else {
     // Any other table: per entry, the last area whose range holds the code
     // and whose rank is valid.
     for (uint32_t c = threadIdx.x; c < 2048; c += blockDim.x) {
-      uint32_t e = 0x8000;
+      uint32_t e = kBadEntry;
 #pragma unroll
       for (int a = 0; a < 8; ++a) {
         if (c >= lo[a] && c < lo[a] + (1u << A.w[a])) {
@@ -1304,9 +1405,153 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
             e = table->rank_to_sym[rank];
         }
       }
-      lut[c] = e;
+      lut[c] = (uint16_t)e;
     }
   }
+}
+
+// One wave's chunks, wave_groups 8-symbol groups per lane, in batches of R
+// = 16 groups, whose output runs (R * kBits bytes per lane, 128 for byte
+// symbols) are stored by kStagePairs consecutive lanes each.
+//
+// kPart = false: all 64 chunks are whole and valid.  kPart = true (chunks
+// past the end, a short last chunk, an invalid chunk: at most the last wave
+// of a valid stream): every lane runs the wave's full count of groups but
+// keeps only its own my_groups: its position stops where its last group
+// ends (later groups decode that place again), a lane without a chunk loads
+// nothing, and discarded groups count no errors and are not stored.
+//
+// Software pipelined: the next group's window is read right after the
+// current chain, so its LDS latency overlaps the current group's LUT
+// gathers and packing.
+//
+// Refill, every eight groups: what was requested eight groups ago goes to
+// the ring and the next superblock is requested, one per lane, which keeps
+// up with 8 bits per symbol.  Every four groups, a wave one of whose lanes'
+// ring does not reach as far as four groups' windows can (kReach, 11-bit
+// codes) takes what is in flight at once, and a lane still short after that
+// gets further superblocks.  The slot a request overwrites lies behind q,
+// since F < q + 3 superblocks.
+//
+// Output: a batch's pairs change owner through the wave's stage, 16 lanes'
+// runs at a time: lane l of a store holds pair l % 8 of chunk l / 8
+// (+ kRuns per store).
+//
+// balance: the launch fits the device at once, so that a wave's end is the
+// kernel's.  The older of the two waves of a SIMD wins every cycle both
+// want, ends first and leaves the other to run alone at little more than
+// half the pair's rate; with a priority that falls with each quarter of the
+// chunk the two end together (256 MiB, C = 2048: 134 -> 130 us; a queue of
+// many groups per workgroup loses 7 % by it).
+template <int kBits, bool kPart>
+__device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, uint32_t tid,
+                                            __amdgpu_buffer_rsrc_t rsrc,
+                                            __amdgpu_buffer_rsrc_t orsrc, uint32_t log2_chunk,
+                                            uint32_t endr, uint32_t sh_lo, uint32_t sh_hi,
+                                            uint32_t my_groups, bool balance) {
+  constexpr uint32_t R = 2 * kStagePairs;       // groups per batch
+  constexpr uint32_t kRuns = 64 / kStagePairs;  // runs per store instruction
+  const uint32_t lane = tid & 63u;
+  const uint32_t wave_groups = 1u << (log2_chunk - 3);
+  const uint32_t part = lane % kStagePairs;
+  // this lane's place in the first runs, and the bytes of kRuns chunks
+  const uint32_t obase = ((lane / kStagePairs) << log2_chunk) / 8 * kBits + part * 2 * kBits;
+  const uint32_t run_step = (kRuns << log2_chunk) / 8 * kBits;
+  // groups kept by each lane (kPart): all in full_lanes, part_groups in
+  // lane part_lane (the short last chunk, the only count in between)
+  const uint64_t full_lanes = __ballot(my_groups == wave_groups);
+  const uint64_t pm = __ballot(my_groups != 0 && my_groups != wave_groups);
+  const uint32_t part_lane = pm ? (uint32_t)__builtin_ctzll(pm) : 64u;
+  const uint32_t part_groups =
+      pm ? (uint32_t)__builtin_amdgcn_readlane((int)my_groups, (int)part_lane) : 0u;
+
+  const uint32_t* ring = S.ring + tid;
+  uint4* stage = (uint4*)(S.ring + kStageBase + (tid >> 6) * kStageWords);
+  Window W = window_read(ring, L.q);
+// Group G of the batch into the pair half OUT, with MID before the next
+// window's read.
+#define QLC_DEC_GROUP(G, OUT, MID)                                               \
+  {                                                                              \
+    uint32_t c[8], e[8], eb = 0;                                                 \
+    const uint32_t adv = decode_chain(W, L.q, sh_lo, sh_hi, c);                  \
+    const bool keep = !kPart || g0 + (G) < my_groups;                            \
+    L.q += keep ? adv : 0u;                                                      \
+    MID;                                                                         \
+    W = window_read(ring, L.q);                                                  \
+    _Pragma("unroll") for (int k = 0; k < 8; ++k) e[k] = S.lut[c[k]];            \
+    OUT = pack_group(e, kPart ? eb : L.errbits);                                 \
+    if (kPart) L.errbits |= keep ? eb : 0u;                                      \
+  }
+#define QLC_DEC_REACH                                                \
+  while (__any(L.have < min(L.q + kReach, endr))) {                  \
+    L.arrive(T, S.ring);                                             \
+    if (!__any(L.have < min(L.q + kReach, endr))) break;             \
+    L.request(T, rsrc, endr, tid);                                   \
+  }
+#define QLC_DEC_REFILL                                               \
+  {                                                                  \
+    L.arrive(T, S.ring);                                             \
+    QLC_DEC_REACH                                                    \
+    L.request(T, rsrc, endr, tid);                                   \
+  }
+#pragma unroll 1
+  for (uint32_t g0 = 0; g0 < wave_groups; g0 += R) {
+    if (balance) {
+      switch (g0 >> (log2_chunk - 5)) {  // the quarter of the chunk
+        case 0: __builtin_amdgcn_s_setprio(3); break;
+        case 1: __builtin_amdgcn_s_setprio(2); break;
+        case 2: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0); break;
+      }
+    }
+    uint4 pr[kStagePairs];
+#pragma unroll
+    for (uint32_t u = 0; u < kStagePairs; u += 4) {
+      uint2 a, b;
+      QLC_DEC_GROUP(2 * u + 0, a, {})
+      QLC_DEC_GROUP(2 * u + 1, b, {})
+      pr[u] = pack_pair<kBits>(a, b);
+      QLC_DEC_GROUP(2 * u + 2, a, {})
+      QLC_DEC_GROUP(2 * u + 3, b, QLC_DEC_REACH)
+      pr[u + 1] = pack_pair<kBits>(a, b);
+      QLC_DEC_GROUP(2 * u + 4, a, {})
+      QLC_DEC_GROUP(2 * u + 5, b, {})
+      pr[u + 2] = pack_pair<kBits>(a, b);
+      QLC_DEC_GROUP(2 * u + 6, a, {})
+      QLC_DEC_GROUP(2 * u + 7, b, QLC_DEC_REFILL)
+      pr[u + 3] = pack_pair<kBits>(a, b);
+    }
+#pragma unroll
+    for (uint32_t h = 0; h < 64 / kStageLanes; ++h) {
+      __builtin_amdgcn_wave_barrier();
+      if (lane / kStageLanes == h) {
+#pragma unroll
+        for (uint32_t p = 0; p < kStagePairs; ++p)
+          stage[(lane % kStageLanes) * (kStageRow / 4) + p] = pr[p];
+      }
+      __builtin_amdgcn_wave_barrier();
+#pragma unroll
+      for (uint32_t k = 0; k < kStageLanes / kRuns; ++k) {
+        const uint32_t c = lane / kStagePairs + kRuns * k;  // chunk of the 16
+        const uint4 v = stage[c * (kStageRow / 4) + part];
+        const uint32_t soff = g0 * kBits + (h * (kStageLanes / kRuns) + k) * run_step;
+        if (!kPart) {
+          store_pair<kBits>(orsrc, obase, soff, v);
+        } else {
+          const uint32_t src = c + kStageLanes * h;
+          const uint32_t ngrp = ((full_lanes >> src) & 1u) ? wave_groups
+                                : src == part_lane ? part_groups : 0u;
+          const uint32_t ga = g0 + 2 * part;
+          if (ga + 1 < ngrp) store_pair<kBits>(orsrc, obase, soff, v);
+          else if (ga < ngrp) store_first<kBits>(orsrc, obase, soff, v);  // the chunk's last whole group
+        }
+      }
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
+#undef QLC_DEC_GROUP
+#undef QLC_DEC_REFILL
+#undef QLC_DEC_REACH
 }
 
 // Decode chunk group `grp` of an n-symbol stream: chunks kDecThreads*grp
@@ -1317,10 +1562,8 @@ template <int kBits>
 __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, uint64_t total,
                              const uint64_t* __restrict__ index_p, uint32_t log2_chunk, uint64_t n,
                              uint8_t* __restrict__ out_p, uint64_t grp, uint32_t sh_lo,
-                             uint32_t sh_hi, DecSmem& S, uint32_t tid) {
+                             uint32_t sh_hi, DecSmem& S, uint32_t tid, bool balance) {
   const QLC_GLOBAL uint64_t* __restrict__ index = (const QLC_GLOBAL uint64_t*)index_p;
-  QLC_GLOBAL uint8_t* __restrict__ out = (QLC_GLOBAL uint8_t*)out_p;
-  const uint32_t lane = tid & 63;
   const uint32_t C = 1u << log2_chunk;
   const uint64_t nchunks = (n + C - 1) >> log2_chunk;
   const uint64_t j = grp * kDecThreads + tid;
@@ -1329,13 +1572,13 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
   bool bad = false;
 
   if (j_wave < nchunks) {
-    // Buffer resource rebased at the wave's first superblock (32-byte aligned):
-    // loads past the end of the stream, or through a corrupt index, return
-    // zeros.
+    // Buffer resource rebased at the wave's first superblock, rounded down to
+    // a whole ring (so that a relative position is also the ring's): loads
+    // past the end of the stream, or through a corrupt index, return zeros.
     const uint64_t stream_bytes = ((total + 31) >> 5) << 2;
     const uint64_t wave_bit = index[j_wave];
     const uint64_t base_sb =
-        (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(wave_bit >> kSbLog2Bits)) |
+        (uint64_t)(__builtin_amdgcn_readfirstlane((uint32_t)(wave_bit >> kSbLog2Bits)) & ~3u) |
         ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(wave_bit >> (32 + kSbLog2Bits))) << 32);
     const uint64_t base_byte = base_sb << (kSbLog2Bits - 3);
     uint64_t avail = stream_bytes > base_byte ? stream_bytes - base_byte : 0;
@@ -1343,6 +1586,12 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
     const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(bits + (base_byte < stream_bytes ? base_byte : 0)), (short)0,
         (int)(uint32_t)avail, 0x00020000);
+    // ... and the output of the wave's chunks
+    QLC_GLOBAL uint8_t* wave_out =
+        (QLC_GLOBAL uint8_t*)out_p + (((j_wave << log2_chunk) * kBits) >> 3);
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
+        (void*)(out_p + (((j_wave << log2_chunk) * kBits) >> 3)), (short)0,
+        (int)((64u << log2_chunk) / 8 * kBits), 0x00020000);
 
     // Per-lane state.  Lanes past the last chunk, or whose index entries
     // are inconsistent, load nothing and keep none of what they decode, but
@@ -1363,213 +1612,49 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
       }
     }
     const bool live = (j < nchunks) && !bad;
+    const uint64_t rel0 = base_sb << kSbLog2Bits;  // positions below are relative to it
+    const uint32_t prel = live ? (uint32_t)(pos0 - rel0) : 0u;
+    const uint32_t endr = live ? (uint32_t)(end - rel0) : 0u;  // nothing loaded past the chunk
     DecLane L;
-    L.ring = S.ring + tid;
-    L.pm1 = (live ? pos0 : 0) - 1;
-    L.sh_lo = sh_lo;
-    L.sh_hi = sh_hi;
     L.errbits = 0;
-    const uint32_t sb0 = (uint32_t)base_sb;         // ring slots follow absolute superblocks
-    uint32_t fsb = live ? (uint32_t)((pos0 >> kSbLog2Bits) - base_sb) : 0;  // next superblock (wave-relative)
+    L.q = prel - 1;
+    L.F = prel & ~(kSbBits - 1);
+    // the first two superblocks (past the chunk's end or the stream's: never
+    // needed, or zeros), which reach beyond the first four groups, and the
+    // request of the third
+    Refill T;
     {
-      constexpr uint32_t kSh = kSbLog2Bits - 3;
-      const Superblock p0 = load_sb(rsrc, live ? (fsb << kSh) : kOobOffset);
-      const Superblock p1 = load_sb(rsrc, live ? ((fsb + 1) << kSh) : kOobOffset);
-      const Superblock p2 = load_sb(rsrc, live ? ((fsb + 2) << kSh) : kOobOffset);
-      const Superblock p3 = load_sb(rsrc, live ? ((fsb + 3) << kSh) : kOobOffset);
-      ring_put(L.ring, sb0 + fsb, p0);
-      ring_put(L.ring, sb0 + fsb + 1, p1);
-      ring_put(L.ring, sb0 + fsb + 2, p2);
-      ring_put(L.ring, sb0 + fsb + 3, p3);
-      fsb += 4;
+      Refill U[2];
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        U[s].issue(rsrc, live ? L.F >> 3 : kOobOffset,
+                   ((L.F & (kRingBits - 1)) >> 5) * kDecLanes + tid, tid);
+        L.F += kSbBits;
+      }
+      L.have = L.F;
+      L.request(T, rsrc, endr, tid);
+      U[0].put(S.ring);
+      U[1].put(S.ring);
     }
-    const uint64_t rel0 = base_sb << kSbLog2Bits;
-    Superblock pa, pb;
-    uint32_t sba = 0, sbb = 0;
-    bool va = false, vb = false;
-    uint2* stage = S.stage + tid * kStageGroups;
-    QLC_GLOBAL uint8_t* o = out + (((j << log2_chunk) * kBits) >> 3);
-    // all lanes of the wave run the same number of groups
-    const uint32_t wave_groups = (uint32_t)(C >> 3);
+    __builtin_amdgcn_wave_barrier();
 
-    // Waves whose 64 chunks are all whole and valid (all but at most the
-    // last wave) take a branch-free path with four register sets in
-    // rotation: a superblock is written to the ring four groups after its
-    // load was issued.  Every kStageGroups groups the wave stores its 64
-    // lanes' output runs (8 * kStageGroups bytes each), kStageGroups
-    // consecutive lanes per run.
-    const bool full_wave = __all(live && my_groups == wave_groups);
-    if (full_wave) {
-      Superblock pc_, pd_;
-      uint32_t sbc = 0, sbd = 0;
-      bool vc = false, vd = false;
-      // bytes: R lanes per output run, one group each; sub-byte symbols: R / 2
-      // lanes per run, two groups (8 or 12 bytes) each
-      constexpr uint32_t R = kStageGroups;              // groups per flush
-      constexpr uint32_t kGpl = kBits == 8 ? 1u : 2u;   // groups per lane per store
-      constexpr uint32_t kLpr = R / kGpl;               // lanes per run
-      constexpr uint32_t kRuns = 64 / kLpr;             // runs per store instruction
-      const uint32_t part = lane % kLpr;
-      QLC_GLOBAL uint8_t* obase =
-          out + ((((j_wave + lane / kLpr) << log2_chunk) * kBits) >> 3) + part * kGpl * kBits;
-      // Software pipelined: the next group's window is read right after the
-      // current chain (and after the ring write it may depend on), so its
-      // LDS latency overlaps the current group's LUT gathers and packing.
-      // Positions are 32-bit, relative to the wave's first superblock.
-      uint32_t q = (uint32_t)(L.pm1 - rel0);
-      const uint32_t endr = (uint32_t)(end - rel0);  // no superblock past the chunk's end
-      const uint32_t* ring = L.ring;
-      const uint32_t rs = (uint32_t)base_sb & 3u;  // ring slot of relative superblock 0
-      Window W = window_read(ring, q + (rs << kSbLog2Bits));
-#define QLC_DEC_UNIT(GI, VAL, SBX, PX)                                                  \
-  {                                                                                     \
-    uint32_t e[8];                                                                      \
-    q += decode_chain(W, q, L.sh_lo, L.sh_hi, S.lut, e);                                \
-    if (VAL) ring_put(L.ring, sb0 + SBX, PX);                                           \
-    W = window_read(ring, q + (rs << kSbLog2Bits));                                     \
-    VAL = (fsb << kSbLog2Bits) < min(q + 1 + kLookaheadBits, endr);                     \
-    SBX = fsb;                                                                          \
-    PX = load_sb(rsrc, VAL ? (fsb << (kSbLog2Bits - 3)) : kOobOffset);                  \
-    fsb += VAL ? 1u : 0u;                                                               \
-    stage[stage_slot((GI), tid)] = pack_out<kBits>(pack_group(e, L.errbits));           \
-  }
-      // One iteration = R groups and their flush, so that the flush sits at
-      // a fixed program point: the waits for loads issued before it then
-      // need not wait for its stores as well.
-#pragma unroll 1
-      for (uint32_t g0 = 0; g0 < wave_groups; g0 += R) {
-#pragma unroll
-        for (uint32_t u = 0; u < R; u += 4) {
-          QLC_DEC_UNIT(g0 + u + 0, va, sba, pa)
-          QLC_DEC_UNIT(g0 + u + 1, vb, sbb, pb)
-          QLC_DEC_UNIT(g0 + u + 2, vc, sbc, pc_)
-          QLC_DEC_UNIT(g0 + u + 3, vd, sbd, pd_)
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (uint32_t k = 0; k < kLpr; ++k) {
-          const uint32_t stid = (tid & ~63u) | (lane / kLpr + kRuns * k);
-          QLC_GLOBAL uint8_t* dst =
-              obase + ((((uint64_t)(kRuns * k) << log2_chunk) * kBits) >> 3) + g0 * kBits;
-          if (kBits == 8) {
-            gstore_u2(dst, S.stage[stid * R + stage_slot(g0 + part, stid)]);
-          } else {
-            const uint2 a = S.stage[stid * R + stage_slot(g0 + 2 * part, stid)];
-            const uint2 b = S.stage[stid * R + stage_slot(g0 + 2 * part + 1, stid)];
-            if (kBits == 4) {
-              gstore_u2(dst, make_uint2(a.x, b.x));
-            } else {  // 12 bytes at a multiple of 12
-              QLC_GLOBAL uint32_t* d32 = (QLC_GLOBAL uint32_t*)dst;
-              d32[0] = a.x;
-              d32[1] = (a.y & 0xFFFFu) | (b.x << 16);
-              d32[2] = (b.x >> 16) | (b.y << 16);
-            }
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-#undef QLC_DEC_UNIT
-      L.pm1 = rel0 + q;
-      if (vc) ring_put(L.ring, sb0 + sbc, pc_);
-      if (vd) ring_put(L.ring, sb0 + sbd, pd_);
-    } else {
-      // Any other wave (chunks past the end, a short last chunk, an invalid
-      // chunk): the same schedule with two register sets, every lane running
-      // the wave's full count of groups but keeping only its own: its
-      // position stops where its last group ends (later groups decode that
-      // place again), a lane without a chunk loads nothing, and discarded
-      // groups count no errors and are not stored.  The group counts are
-      // wave-uniform: all (lanes in full_lanes), none, or part_groups in
-      // lane part_lane (the short last chunk, the only count in between).
-      constexpr uint32_t R = kStageGroups;
-      constexpr uint32_t kGpl = kBits == 8 ? 1u : 2u;
-      constexpr uint32_t kLpr = R / kGpl;
-      constexpr uint32_t kRuns = 64 / kLpr;
-      const uint32_t part = lane % kLpr;
-      QLC_GLOBAL uint8_t* obase =
-          out + ((((j_wave + lane / kLpr) << log2_chunk) * kBits) >> 3) + part * kGpl * kBits;
-      const uint64_t full_lanes = __ballot(my_groups == wave_groups);
-      const uint64_t pm = __ballot(my_groups != 0 && my_groups != wave_groups);
-      const uint32_t part_lane = pm ? (uint32_t)__builtin_ctzll(pm) : 64u;
-      const uint32_t part_groups =
-          pm ? (uint32_t)__builtin_amdgcn_readlane((int)my_groups, (int)part_lane) : 0u;
-      uint32_t q = (uint32_t)(L.pm1 - rel0);
-      const uint32_t endr = live ? (uint32_t)(end - rel0) : 0u;
-      const uint32_t* ring = L.ring;
-      const uint32_t rs = (uint32_t)base_sb & 3u;
-      Window W = window_read(ring, q + (rs << kSbLog2Bits));
-#define QLC_DEC_UNIT_P(GI, VAL, SBX, PX)                                                \
-  {                                                                                     \
-    uint32_t e[8];                                                                      \
-    const uint32_t adv = decode_chain(W, q, L.sh_lo, L.sh_hi, S.lut, e);                \
-    const bool keep = (GI) < my_groups;                                                 \
-    q += keep ? adv : 0u;                                                               \
-    if (VAL) ring_put(L.ring, sb0 + SBX, PX);                                           \
-    W = window_read(ring, q + (rs << kSbLog2Bits));                                     \
-    VAL = (fsb << kSbLog2Bits) < min(q + 1 + kLookaheadBits, endr);                     \
-    SBX = fsb;                                                                          \
-    PX = load_sb(rsrc, VAL ? (fsb << (kSbLog2Bits - 3)) : kOobOffset);                  \
-    fsb += VAL ? 1u : 0u;                                                               \
-    uint32_t eb = 0;                                                                    \
-    stage[stage_slot((GI), tid)] = pack_out<kBits>(pack_group(e, eb));                  \
-    L.errbits |= keep ? eb : 0u;                                                        \
-  }
-#pragma unroll 1
-      for (uint32_t g0 = 0; g0 < wave_groups; g0 += R) {
-#pragma unroll
-        for (uint32_t u = 0; u < R; u += 2) {
-          QLC_DEC_UNIT_P(g0 + u + 0, va, sba, pa)
-          QLC_DEC_UNIT_P(g0 + u + 1, vb, sbb, pb)
-        }
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll 1
-        for (uint32_t k = 0; k < kLpr; ++k) {
-          const uint32_t src = lane / kLpr + kRuns * k;  // lane (chunk) whose run is stored
-          const uint32_t stid = (tid & ~63u) | src;
-          const uint32_t ngrp = ((full_lanes >> src) & 1u) ? wave_groups
-                                : src == part_lane ? part_groups : 0u;
-          QLC_GLOBAL uint8_t* dst =
-              obase + ((((uint64_t)(kRuns * k) << log2_chunk) * kBits) >> 3) + g0 * kBits;
-          if (kBits == 8) {
-            if (g0 + part < ngrp) gstore_u2(dst, S.stage[stid * R + stage_slot(g0 + part, stid)]);
-          } else {
-            // two groups (8 or 12 bytes at a multiple of 8 or 12), or only
-            // the first when it is the chunk's last whole group
-            const uint32_t ga = g0 + 2 * part;
-            const uint2 a = S.stage[stid * R + stage_slot(ga, stid)];
-            const uint2 b = S.stage[stid * R + stage_slot(ga + 1, stid)];
-            QLC_GLOBAL uint32_t* d32 = (QLC_GLOBAL uint32_t*)dst;
-            if (ga < ngrp) d32[0] = a.x;
-            if (ga + 1 < ngrp) {
-              if (kBits == 4) {
-                d32[1] = b.x;
-              } else {
-                d32[1] = (a.y & 0xFFFFu) | (b.x << 16);
-                d32[2] = (b.x >> 16) | (b.y << 16);
-              }
-            } else if (kBits == 6 && ga < ngrp) {
-              *(QLC_GLOBAL uint16_t*)(dst + 4) = (uint16_t)a.y;
-            }
-          }
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-#undef QLC_DEC_UNIT_P
-      // a lane that decoded no group keeps its 64-bit position (q holds it
-      // modulo 2^32, which for the stream's first bit, pm1 = -1, is not it)
-      if (my_groups) L.pm1 = rel0 + q;
-    }
-    if (va) ring_put(L.ring, sb0 + sba, pa);
-    if (vb) ring_put(L.ring, sb0 + sbb, pb);
+    // Waves whose 64 chunks are all whole and valid are all but at most the
+    // last of a valid stream.
+    if (__all(live && my_groups == (C >> 3)))
+      decode_wave<kBits, false>(L, T, S, tid, rsrc, orsrc, log2_chunk, endr, sh_lo, sh_hi,
+                                my_groups, balance);
+    else
+      decode_wave<kBits, true>(L, T, S, tid, rsrc, orsrc, log2_chunk, endr, sh_lo, sh_hi,
+                               my_groups, balance);
+    L.arrive(T, S.ring);
+    // the position, in 64 bits (a lane that decoded no group is where it began)
+    uint64_t pos = my_groups ? rel0 + L.q + 1 : pos0;
     if (live && rem) {  // final partial group of the last chunk
-      const uint32_t q = (uint32_t)L.pm1;
-      const uint32_t wi = (q >> 5) & 31u;
-      const uint32_t* rr = L.ring + wi * kDecLanes;
-      const uint32_t w0 = __builtin_bswap32(rr[0]), w1 = __builtin_bswap32(rr[kDecLanes]);
-      const uint32_t w2 = __builtin_bswap32(rr[2 * kDecLanes]), w3 = __builtin_bswap32(rr[3 * kDecLanes]);
-      uint32_t A = __builtin_amdgcn_alignbit(w0, w1, ~q);
-      uint32_t B = __builtin_amdgcn_alignbit(w1, w2, ~q);
-      uint32_t Cw = __builtin_amdgcn_alignbit(w2, w3, ~q);
+      const Window W = window_read(S.ring + tid, L.q);
+      uint32_t A = __builtin_amdgcn_alignbit(W.w0, W.w1, ~L.q);
+      uint32_t B = __builtin_amdgcn_alignbit(W.w1, W.w2, ~L.q);
+      uint32_t Cw = __builtin_amdgcn_alignbit(W.w2, W.w3, ~L.q);
+      QLC_GLOBAL uint8_t* o = wave_out + ((uint64_t)(tid & 63u) << log2_chunk) / 8 * kBits;
       uint64_t acc = 0;  // the partial group, packed (sub-byte symbols)
       for (uint32_t k = 0; k < rem; ++k) {
         const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, A, 29);
@@ -1581,14 +1666,14 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
         A = __builtin_amdgcn_alignbit(A, B, s);
         B = __builtin_amdgcn_alignbit(B, Cw, s);
         Cw = __builtin_amdgcn_alignbit(Cw, 0u, s);
-        L.pm1 += 32u - s;
+        pos += 32u - s;
       }
       if (kBits != 8) {  // whole bytes; the last one zero padded
         QLC_GLOBAL uint8_t* d = o + my_groups * kBits;
         for (uint32_t b = 0; b < (rem * kBits + 7) / 8; ++b) d[b] = (uint8_t)(acc >> (8 * b));
       }
     }
-    if (live) bad = (L.errbits & 0x8000u) || (L.pm1 + 1 != end);
+    if (live) bad = (L.errbits & kBadMask) || pos != end;
   }
   return bad;
 }
@@ -1598,7 +1683,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
     const uint8_t* __restrict__ bits, const uint64_t* __restrict__ total_p,
     const uint64_t* __restrict__ index, uint32_t log2_chunk,
     const qlc_table* __restrict__ table, uint64_t n, uint8_t* __restrict__ out,
-    uint32_t* __restrict__ err_out, WsHeader* __restrict__ hdr) {
+    uint32_t* __restrict__ err_out, WsHeader* __restrict__ hdr, bool balance) {
   __shared__ DecSmem S;
   const uint32_t tid = threadIdx.x;
   uint32_t sh_lo, sh_hi;
@@ -1611,7 +1696,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
   // a table of another alphabet is refused (nothing decoded)
   if (table_ok) {
     const bool bad = decode_block<kBits>(bits, *total_p, index, log2_chunk, n, out, blockIdx.x,
-                                         sh_lo, sh_hi, S, tid);
+                                         sh_lo, sh_hi, S, tid, balance);
     set_error_wave(&hdr->dec_err, QLC_ERR_CORRUPT_STREAM, bad);
   } else if (tid == 0) {
     set_error(&hdr->dec_err, QLC_ERR_INVALID_ARGUMENT);
@@ -1680,7 +1765,7 @@ constexpr uint32_t kSplitMaxChunks = kSplitSyms >> 8;         // chunks per work
 constexpr uint32_t kSplitWarmBits = 512;                      // walked before a piece, not counted
 
 struct SplitSmem {
-  uint32_t lut[2048];
+  uint16_t lut[2048];
   uint32_t span[kSplitSpanWords];         // stream words from base_bit on (memory byte order)
   uint8_t out[kSplitSyms];                // decoded symbols, one per byte
   uint32_t xs[2][kSplitThreads];          // walk exits, by round parity
@@ -1704,15 +1789,16 @@ __device__ __forceinline__ uint32_t split_code_len(const uint32_t* span, uint32_
   return 32u - __builtin_amdgcn_perm(sh_hi, sh_lo, sel);
 }
 
-// The four words holding stream bits rel .. rel + 95 (and q for the chain).
+// The four words holding stream bits rel .. rel + 95, most-significant-first
+// (and q for the chain).
 __device__ __forceinline__ Window split_window(const uint32_t* span, uint32_t rel, uint32_t& q) {
   q = rel + kSplitQOff;
   const uint32_t* rr = span + (q >> 5);
   Window w;
-  w.w0 = rr[0];
-  w.w1 = rr[1];
-  w.w2 = rr[2];
-  w.w3 = rr[3];
+  w.w0 = __builtin_bswap32(rr[0]);
+  w.w1 = __builtin_bswap32(rr[1]);
+  w.w2 = __builtin_bswap32(rr[2]);
+  w.w3 = __builtin_bswap32(rr[3]);
   return w;
 }
 
@@ -1723,11 +1809,9 @@ __device__ __forceinline__ uint32_t split_walk(const uint32_t* span, uint32_t x,
   while (x < end) {
     uint32_t q;
     const Window W = split_window(span, x, q);
-    const uint32_t w0 = __builtin_bswap32(W.w0), w1 = __builtin_bswap32(W.w1);
-    const uint32_t w2 = __builtin_bswap32(W.w2), w3 = __builtin_bswap32(W.w3);
-    uint32_t A = __builtin_amdgcn_alignbit(w0, w1, ~q);
-    uint32_t B = __builtin_amdgcn_alignbit(w1, w2, ~q);
-    uint32_t Cw = __builtin_amdgcn_alignbit(w2, w3, ~q);
+    uint32_t A = __builtin_amdgcn_alignbit(W.w0, W.w1, ~q);
+    uint32_t B = __builtin_amdgcn_alignbit(W.w1, W.w2, ~q);
+    uint32_t Cw = __builtin_amdgcn_alignbit(W.w2, W.w3, ~q);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {  // at most 88 of the window's 96 bits
       const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, A, 29);
@@ -1955,9 +2039,11 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
     Window W = split_window(S.span, pos, q);
     const uint32_t full = cnt >> 3, rem = cnt & 7u;
     for (uint32_t k0 = 0; k0 < full; ++k0, dst += 8) {
-      uint32_t e[8];
-      pos += decode_chain(W, q, sh_lo, sh_hi, S.lut, e);
+      uint32_t c[8], e[8];
+      pos += decode_chain(W, q, sh_lo, sh_hi, c);
       W = split_window(S.span, pos, q);  // the next group's window, read early
+#pragma unroll
+      for (uint32_t k = 0; k < 8; ++k) e[k] = S.lut[c[k]];
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k) {
         dst[k] = (uint8_t)e[k];
@@ -1965,8 +2051,10 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
       }
     }
     if (rem) {
-      uint32_t e[8];
-      decode_chain(W, q, sh_lo, sh_hi, S.lut, e);
+      uint32_t c[8], e[8];
+      decode_chain(W, q, sh_lo, sh_hi, c);
+#pragma unroll
+      for (uint32_t k = 0; k < 7; ++k) e[k] = S.lut[c[k]];
 #pragma unroll
       for (uint32_t k = 0; k < 7; ++k) {
         if (k < rem) {
@@ -1975,7 +2063,7 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
         }
       }
     }
-    bad = (errbits & 0x8000u) != 0;
+    bad = (errbits & kBadMask) != 0;
   }
   lds_barrier();
 
@@ -2353,13 +2441,16 @@ union BatchDecSmem {
 };
 static_assert(offsetof(DecSmem, lut) == 0 && offsetof(SplitSmem, lut) == 0, "shared LUT");
 static_assert(kSplitThreads == kDecThreads, "one block size");
+static_assert(sizeof(SplitSmem) <= offsetof(DecSmem, ring) + 4 * kStageBase, "the ticket's word");
 
 template <int kBits>
-__global__ __launch_bounds__(kDecThreads) void k_decode_batched(
+__global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
     const qlc_job* __restrict__ jobs, uint32_t log2_chunk, BatchHeader* __restrict__ hdr,
     const BatchJobState* __restrict__ js, const uint32_t* __restrict__ grp_job) {
   __shared__ BatchDecSmem S;
-  __shared__ uint32_t s_ticket;
+  // the ticket lives in the padding of the first staged run (neither layout
+  // uses that word), which keeps two workgroups on a CU
+  uint32_t& s_ticket = S.lane.ring[kStageBase + kStagePairs * 4];
   const uint32_t tid = threadIdx.x;
   const uint32_t units = hdr->units;
   if (blockIdx.x >= units) return;  // (as in the encoder: only as many workgroups as items)
@@ -2389,7 +2480,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode_batched(
               ? split_block<kBits>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                    jb.out, unit, nullptr, L, S.split, opaque_tid())
               : decode_block<kBits>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
-                                    jb.out, unit, L.sh_lo, L.sh_hi, S.lane, opaque_tid());
+                                    jb.out, unit, L.sh_lo, L.sh_hi, S.lane, opaque_tid(), false);
       set_error_wave(jb.err, QLC_ERR_CORRUPT_STREAM, bad);
     } else if (tid == 0) {
       set_error(jb.err, QLC_ERR_INVALID_ARGUMENT);  // a table of another alphabet
@@ -2478,8 +2569,10 @@ hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const ui
   const uint64_t nchunks = (n + (1ull << log2_chunk) - 1) >> log2_chunk;
   uint64_t blocks = (nchunks + kDecThreads - 1) / kDecThreads;
   if (blocks < 1) blocks = 1;
+  // two workgroups fit a compute unit; fewer leave nothing to balance
+  const bool balance = blocks > 256 && blocks <= 512;
   QLC_LAUNCH_BITS(bits, k_decode, dim3((uint32_t)blocks), dim3(kDecThreads), bits_in, total,
-                  index, log2_chunk, table, n, out, err_out, hdr);
+                  index, log2_chunk, table, n, out, err_out, hdr, balance);
   return hipGetLastError();
 }
 
