@@ -251,17 +251,18 @@ qlc_status qlc_decode(const uint8_t* bits, const uint64_t* total_bits,
  * are found by walking lengths alone):
  *   QLC_DECODER_LANE   one lane walks each chunk from its index entry; the
  *                      rate for tensors of many chunks (n / C >= 2^17);
- *   QLC_DECODER_SPLIT  C / 64 lanes per chunk (C <= 16384, else
+ *   QLC_DECODER_SPLIT  C / 64 lanes per chunk, or C / 32 for small tensors
+ *                      (C <= 16384, else
  *                      QLC_ERR_INVALID_ARGUMENT): each lane walks the code
  *                      lengths of one piece of the chunk's bits from a
  *                      guessed start, the lanes correct their starts from
  *                      their neighbours' exits, then each decodes about 64
- *                      codes; latency for tensors of few chunks;
+ *                      (32) codes; latency for tensors of few chunks;
  *   QLC_DECODER_AUTO   the one qlc_decode / qlc_decode_sym use: the decoder
  *                      with the shorter estimated time, from models of both
- *                      fitted on MI355X (256 MiB down to 1 Mi symbols):
- *                      LANE  max(14.6 us + 36.7 ns * C, 0.615 ps * n),
- *                      SPLIT 21.3 us + 1.235 ps * n (only for C <= 16384).
+ *                      fitted on MI355X (256 Mi down to 64 Ki symbols):
+ *                      LANE  max(5.2 us + 33.1 ns * C, 5 us + 0.62 ps * n),
+ *                      SPLIT 9.5 us + 1.0 ps * n (only for C <= 16384).
  * symbol_bits as in the *_sym entry points below (8 for bytes); other
  * arguments and errors as qlc_decode. */
 typedef enum qlc_decoder {

@@ -363,17 +363,18 @@ qlc_status qlc_compress_noalloc(const uint8_t* in, uint64_t n, qlc_layout_mode m
 }
 
 // The decoder with the shorter estimated time (ns), from two-term models
-// fitted to measured decode times on MI355X: one lane per chunk walks C
-// codes in sequence (a fixed cost plus 36.7 ns per code) unless the chunks
-// fill the device, where it takes 0.615 ps per symbol (1.63 TB/s); the
-// split decoder costs 21.3 us plus 1.235 ps per symbol (1 to 128 Mi
-// symbols, 512-bit warm-up).
+// fitted to measured decode times on MI355X (64 Ki to 256 Mi symbols, C =
+// 256 to 8192): one lane per chunk walks C codes in sequence (a fixed cost
+// plus 33.1 ns per code; C = 256 13.7 us, 2048 72 us) unless the chunks fill
+// the device, where it takes 0.62 ps per symbol (64 Mi symbols at C = 256:
+// 46.5 us); the split decoder costs 9.5 us plus 1.0 ps per symbol (1 Mi
+// symbols 10.1 us, 9 Mi 18.3, 64 Mi 75).
 static qlc_decoder auto_decoder(uint64_t n, uint32_t log2c) {
   if (log2c > kSplitMaxLog2Chunk) return QLC_DECODER_LANE;
   const uint64_t C = 1ull << log2c;
-  const uint64_t lane_walk = 14600 + C * 367 / 10, lane_rate = n * 615 / 1000000;
+  const uint64_t lane_walk = 5200 + C * 331 / 10, lane_rate = 5000 + n * 62 / 100000;
   const uint64_t lane = lane_walk > lane_rate ? lane_walk : lane_rate;
-  const uint64_t split = 21300 + n * 1235 / 1000000;
+  const uint64_t split = 9500 + n / 1000;
   return split < lane ? QLC_DECODER_SPLIT : QLC_DECODER_LANE;
 }
 

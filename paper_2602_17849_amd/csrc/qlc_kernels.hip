@@ -1196,21 +1196,37 @@ __device__ __forceinline__ uint32_t decode_chain(const Window& W, uint32_t q, ui
   return (0u - ssum) & 0xFFu;  // 256 - sum of (32 - length), at most 88
 }
 
-// LUT entry of an invalid suffix, and the invalid flags of a packed pair of
-// entries.
+// LUT entry of an invalid suffix, and the invalid flags that pack_group
+// accumulates for an alphabet (single entries' among them).
 constexpr uint32_t kBadEntry = 0x8000u;
-constexpr uint32_t kBadMask = kBadEntry | (kBadEntry << 16);
+template <int kBits>
+__device__ constexpr uint32_t bad_mask() {
+  return kBits == 8 ? kBadEntry | (kBadEntry << 16) : kBadEntry | (kBadEntry << kBits);
+}
 
-// The 8 decoded bytes packed little-endian; the entries' invalid flags are
-// accumulated in errbits.
+// Eight entries packed: 8 bytes, little-endian (byte symbols); 4 bytes of
+// nibbles in x (4-bit symbols); two 24-bit halves of four symbols each in x
+// and y (6-bit symbols).  The entries' invalid flags are accumulated in
+// errbits; the small alphabets' flags also land in the packed words, whose
+// value does not matter then.
+template <int kBits>
 __device__ __forceinline__ uint2 pack_group(const uint32_t (&e)[8], uint32_t& errbits) {
-  const uint32_t p0 = (e[1] << 16) | e[0], p1 = (e[3] << 16) | e[2];
-  const uint32_t p2 = (e[5] << 16) | e[4], p3 = (e[7] << 16) | e[6];
-  uint2 r;
-  r.x = __builtin_amdgcn_perm(p1, p0, 0x06040200u);
-  r.y = __builtin_amdgcn_perm(p3, p2, 0x06040200u);
+  constexpr int kSh = kBits == 8 ? 16 : kBits;
+  const uint32_t p0 = (e[1] << kSh) | e[0], p1 = (e[3] << kSh) | e[2];
+  const uint32_t p2 = (e[5] << kSh) | e[4], p3 = (e[7] << kSh) | e[6];
   errbits |= p0 | p1;
   errbits |= p2 | p3;
+  uint2 r;
+  if (kBits == 8) {
+    r.x = __builtin_amdgcn_perm(p1, p0, 0x06040200u);
+    r.y = __builtin_amdgcn_perm(p3, p2, 0x06040200u);
+  } else if (kBits == 6) {
+    r.x = (p1 << 12) | p0;
+    r.y = (p3 << 12) | p2;
+  } else {
+    r.x = (((p3 << 8) | p2) << 16) | ((p1 << 8) | p0);
+    r.y = 0u;
+  }
   return r;
 }
 
@@ -1249,14 +1265,13 @@ __device__ __forceinline__ void store_group(QLC_GLOBAL uint8_t* p, uint2 v) {
   }
 }
 
-// Two consecutive groups (pack_group's words) in the output format: 16, 8 or
-// 12 bytes in the first words of a uint4.
+// Two consecutive groups (from pack_group) in the output format: 16, 8 or 12
+// bytes in the first words of a uint4.
 template <int kBits>
-__device__ __forceinline__ uint4 pack_pair(uint2 g0, uint2 g1) {
-  const uint2 a = pack_out<kBits>(g0), b = pack_out<kBits>(g1);
+__device__ __forceinline__ uint4 pack_pair(uint2 a, uint2 b) {
   if (kBits == 8) return make_uint4(a.x, a.y, b.x, b.y);
   if (kBits == 4) return make_uint4(a.x, b.x, 0u, 0u);
-  return make_uint4(a.x, (a.y & 0xFFFFu) | (b.x << 16), (b.x >> 16) | (b.y << 16), 0u);
+  return make_uint4((a.y << 24) | a.x, (b.x << 16) | (a.y >> 8), (b.y << 8) | (b.x >> 16), 0u);
 }
 
 // Store a pair's 2 * kBits bytes at byte off + soff (soff wave-uniform) of a
@@ -1315,9 +1330,9 @@ __device__ __forceinline__ void table_to_lds(const qlc_table* __restrict__ t, ql
 // bits (byte i of sh_hi:sh_lo = 32 - prefix bits - width of the area the
 // top bits name).  A table whose areas 4..7 (or 2..7) are marked 0xFF has a
 // 2-bit (1-bit) area code: top bits 2a and 2a + 1 (4a .. 4a + 3) all name
-// area a, so the decode chain is the same for every prefix width.  Any
-// block size; every thread of the block calls it (it may synchronise the
-// block), and the caller synchronises again before using the LUT.
+// area a, so the decode chain is the same for every prefix width.  `table`
+// is the LDS copy.  All kDecThreads threads of the block call it (it
+// synchronises them), and the caller synchronises again before using the LUT.
 // The per-area fields of a table (width, offset, first, count: 48
 // contiguous bytes), read with three 16-byte loads.
 static_assert(offsetof(qlc_table, width) == 1024 && offsetof(qlc_table, offset) == 1032 &&
@@ -1347,61 +1362,88 @@ __device__ __forceinline__ AreaFields read_areas(const qlc_table* __restrict__ t
   return f;
 }
 
+//
+// The areas are worked on by lanes 0..7 of each wave (and again in each other
+// eight lanes), one area each; done area by area in every lane this took
+// 600 instructions, 1.5 us of a lone wave, before a decode could begin.
+// d: the gcd of the code lengths of the areas that hold symbols.
 __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ table, uint16_t* lut,
-                              uint32_t& sh_lo, uint32_t& sh_hi) {
-  sh_lo = 0;
-  sh_hi = 0;
-  const AreaFields A = read_areas(table);
-  const uint32_t p = A.p, na = A.na;
-  uint32_t lo[8];
-  bool layered = true;  // widths non-decreasing, rank ranges back to back
-  uint32_t f = 0;
+                                              uint32_t& sh_lo, uint32_t& sh_hi, uint32_t& d) {
+  const uint32_t tid = threadIdx.x;
+  // every entry invalid: 256 threads, 16 bytes each
+  constexpr uint32_t kBad2 = kBadEntry | (kBadEntry << 16);
+  ((uint4*)lut)[tid] = make_uint4(kBad2, kBad2, kBad2, kBad2);
+
+  const uint32_t i = tid & 7u;  // this lane's area
+  const uint32_t w_raw = table->width[i];
+  const uint32_t ff = (uint32_t)__ballot(w_raw == 0xFFu);
+  const uint32_t p = !(ff & 0x10u) ? 3u : !(ff & 4u) ? 2u : 1u;  // area-code bits
+  const uint32_t na = 1u << p;
+  const bool used = i < na;
+  const uint32_t w = used ? min(w_raw, 8u) : 0u;  // keeps codes < 2048
+  const uint32_t cnt = used ? (uint32_t)table->count[i] : 0u;
+  const uint32_t first = used ? (uint32_t)table->first[i] : 0xFFFFu;
+  // ranks before the area (a scan over the row's first eight lanes)
+#define QLC_ROW_SHR(v, n) \
+  ((uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), 0x110 + (n), 0xf, 0xf, true))
+  uint32_t incl = cnt;
+  incl += QLC_ROW_SHR(incl, 1);
+  incl += QLC_ROW_SHR(incl, 2);
+  incl += QLC_ROW_SHR(incl, 4);
+  const uint32_t w_before = QLC_ROW_SHR(w, 1);
+  const uint32_t ok =
+      (uint32_t)__ballot(!used || (first == incl - cnt && (i == 0 || w >= w_before)));
+#undef QLC_ROW_SHR
+  const uint32_t f = (uint32_t)__builtin_amdgcn_readlane((int)incl, 7);
+  // widths non-decreasing, rank ranges back to back
+  const bool layered = (ok & 0xFFu) == 0xFFu && f <= 256u;
+  // byte i of the shift table: the area that the top bits i name, i >> (3 - p)
+  uint32_t v = (32u - p - min((uint32_t)table->width[i >> (3u - p)], 8u)) << (8u * (i & 3u));
+  uint32_t lens = used && cnt != 0 ? 1u << (p + w) : 0u;
+#define QLC_OR_DPP(v, ctrl) \
+  v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, true)
+  QLC_OR_DPP(v, 0xB1);      // quad_perm [1,0,3,2]
+  QLC_OR_DPP(v, 0x4E);      // quad_perm [2,3,0,1]
+  QLC_OR_DPP(lens, 0xB1);
+  QLC_OR_DPP(lens, 0x4E);
+  QLC_OR_DPP(lens, 0x141);  // row_half_mirror
+#undef QLC_OR_DPP
+  sh_lo = (uint32_t)__builtin_amdgcn_readlane((int)v, 0);
+  sh_hi = (uint32_t)__builtin_amdgcn_readlane((int)v, 4);
+  // the largest k that divides every length (lengths are at most 11)
+  lens = (uint32_t)__builtin_amdgcn_readfirstlane((int)lens);
+  d = 1;
 #pragma unroll
-  for (int a = 0; a < 8; ++a) {
-    lo[a] = (uint32_t)a << A.w[a];
-    if ((uint32_t)a < na) {
-      layered = layered && A.first[a] == f && (a == 0 || A.w[a] >= A.w[a - 1]);
-      f += A.cnt[a];
-    }
-  }
-  layered = layered && f <= 256;
+  for (uint32_t k = 2; k <= QLC_MAX_CODE_BITS; ++k) {
+    uint32_t mult = 0;
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    // area named by top bits i: i >> (3 - p), selected without indexing
-    // the array by a run-time value (which would put it in scratch memory)
-    const uint32_t wi = p == 3 ? A.w[i] : p == 2 ? A.w[i >> 1] : A.w[i >> 2];
-    const uint32_t sft = 32u - p - wi;
-    if (i < 4) sh_lo |= sft << (8 * i);
-    else sh_hi |= sft << (8 * (i - 4));
+    for (uint32_t m = k; m <= QLC_MAX_CODE_BITS; m += k) mult |= 1u << m;
+    if (lens != 0 && (lens & ~mult) == 0) d = k;
   }
+  lds_barrier();
   if (layered) {
     // Areas' code ranges are disjoint and every rank lies in one area, so
-    // each rank's code is its own LUT entry: clear, then one write per rank.
-    for (uint32_t c = threadIdx.x; c < 2048; c += blockDim.x) lut[c] = (uint16_t)kBadEntry;
-    lds_barrier();
-    for (uint32_t r = threadIdx.x; r < f; r += blockDim.x) {
-      uint32_t a = 0;
+    // each rank's code is its own LUT entry: one write per rank.
+    uint32_t a = 0;
 #pragma unroll
-      for (int k = 1; k < 8; ++k) a += ((uint32_t)k < na && A.first[k] <= r) ? 1u : 0u;
-      uint32_t wa = A.w[0], oa = A.off[0];
-#pragma unroll
-      for (int k = 1; k < 8; ++k) {
-        wa = a == (uint32_t)k ? A.w[k] : wa;
-        oa = a == (uint32_t)k ? A.off[k] : oa;
-      }
-      const uint32_t suffix = r - oa;
-      if (suffix < (1u << wa)) lut[(a << wa) + suffix] = (uint16_t)table->rank_to_sym[r];
-    }
+    for (int k = 1; k < 8; ++k)
+      a += (uint32_t)__builtin_amdgcn_readlane((int)first, k) <= tid ? 1u : 0u;
+    const uint32_t wa = min((uint32_t)table->width[a], 8u);
+    const uint32_t suffix = tid - table->offset[a];
+    if (tid < f && suffix < (1u << wa))
+      lut[(a << wa) + suffix] = (uint16_t)table->rank_to_sym[tid];
   } else {
     // Any other table: per entry, the last area whose range holds the code
     // and whose rank is valid.
-    for (uint32_t c = threadIdx.x; c < 2048; c += blockDim.x) {
+    const AreaFields A = read_areas(table);
+    for (uint32_t c = tid; c < 2048; c += kDecThreads) {
       uint32_t e = kBadEntry;
 #pragma unroll
-      for (int a = 0; a < 8; ++a) {
-        if (c >= lo[a] && c < lo[a] + (1u << A.w[a])) {
-          const uint32_t rank = A.off[a] + (c - lo[a]);
-          if (rank >= A.first[a] && rank < A.first[a] + A.cnt[a] && rank < 256)
+      for (int k = 0; k < 8; ++k) {
+        const uint32_t lo = (uint32_t)k << A.w[k];
+        if (c >= lo && c < lo + (1u << A.w[k])) {
+          const uint32_t rank = A.off[k] + (c - lo);
+          if (rank >= A.first[k] && rank < A.first[k] + A.cnt[k] && rank < 256)
             e = table->rank_to_sym[rank];
         }
       }
@@ -1479,7 +1521,7 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
     MID;                                                                         \
     W = window_read(ring, L.q);                                                  \
     _Pragma("unroll") for (int k = 0; k < 8; ++k) e[k] = S.lut[c[k]];            \
-    OUT = pack_group(e, kPart ? eb : L.errbits);                                 \
+    OUT = pack_group<kBits>(e, kPart ? eb : L.errbits);                          \
     if (kPart) L.errbits |= keep ? eb : 0u;                                      \
   }
 #define QLC_DEC_REACH                                                \
@@ -1673,7 +1715,7 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
         for (uint32_t b = 0; b < (rem * kBits + 7) / 8; ++b) d[b] = (uint8_t)(acc >> (8 * b));
       }
     }
-    if (live) bad = (L.errbits & kBadMask) || pos != end;
+    if (live) bad = (L.errbits & bad_mask<kBits>()) || pos != end;
   }
   return bad;
 }
@@ -1686,11 +1728,11 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
     uint32_t* __restrict__ err_out, WsHeader* __restrict__ hdr, bool balance) {
   __shared__ DecSmem S;
   const uint32_t tid = threadIdx.x;
-  uint32_t sh_lo, sh_hi;
+  uint32_t sh_lo, sh_hi, d;
   qlc_table* tl = (qlc_table*)S.ring;  // the ring is free until the decode starts
   table_to_lds(table, tl, tid);
   __syncthreads();
-  build_dec_lut(tl, S.lut, sh_lo, sh_hi);
+  build_dec_lut(tl, S.lut, sh_lo, sh_hi, d);
   const bool table_ok = mode_symbol_bits(tl->mode) == kBits;
   __syncthreads();
   // a table of another alphabet is refused (nothing decoded)
@@ -1720,10 +1762,11 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
 // With one lane per chunk (k_decode) a tensor of few chunks leaves the
 // device idle: a 1 Mi-symbol tensor at C = 2048 is 512 chunks, i.e. 512
 // lanes, each walking 2048 codes one after the other.  Here a workgroup
-// takes kSplitSyms (16384) symbols, i.e. 16384 / C whole chunks, and gives
-// every chunk G = C / 64 lanes (C <= 16384), about 64 codes per lane:
+// takes 256 * 2^kL symbols (kL = 6; 5 for small tensors), i.e. whole chunks,
+// and gives every chunk G = C / 2^kL lanes, about 2^kL codes per lane:
 //   1. the workgroup's stretch of the bitstream is copied into LDS with
-//      coalesced 16-byte loads (each stream byte is read once);
+//      coalesced 16-byte loads (each stream byte is read once), byte-swapped
+//      to most-significant-first words on the way;
 //   2. lane g of a chunk takes the g-th of G equal pieces of the chunk's
 //      bits and walks code lengths only (a code's length follows from its
 //      area code alone), starting kSplitWarmBits before its piece as if a
@@ -1733,12 +1776,13 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
 //      that start in its piece; it records where its walk enters and leaves
 //      the piece and how many codes it passed in between;
 //   3. correction rounds: a lane whose start differs from the point where
-//      the previous lane's walk left the previous piece walks again from
-//      that point, in step with its old path, until the two paths meet
-//      (from there on they coincide) or the piece ends.  After round r the
+//      the previous lane's walk left the previous piece walks its piece
+//      again from that point (in step with its old path, one code of either
+//      at a time, until the two meet, it cost the few workgroups that have
+//      such a lane 3.5 us).  After round r the
 //      first r + 1 lanes of every chunk are exact; the rounds stop when no
 //      lane's exit changed, so after at most G + 1 rounds, and in practice
-//      the two paths meet within a few codes and one round suffices;
+//      one round suffices;
 //   4. a scan of the code counts gives every lane the position of its first
 //      symbol; the lane decodes its codes through the code-word LUT into an
 //      LDS copy of the workgroup's output, which is then stored with
@@ -1752,98 +1796,111 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
 // lies outside its area, or its index entries are out of order.
 // ===========================================================================
 constexpr int kSplitThreads = 256;
-constexpr uint32_t kSplitLog2Syms = kSplitMaxLog2Chunk;      // symbols per workgroup
-constexpr uint32_t kSplitSyms = 1u << kSplitLog2Syms;
 constexpr uint32_t kMaxCodeBits = 11;                         // 3-bit area code + 8-bit suffix
-constexpr uint32_t kSplitCapBits = kSplitSyms * kMaxCodeBits + 128;  // + alignment of the base
 constexpr uint32_t kSplitPadWords = 4;                        // zero words before the stream copy
-constexpr uint32_t kSplitLoadWords = ((kSplitCapBits + 31) / 32 + 4 + 3) & ~3u;
-constexpr uint32_t kSplitSpanWords = kSplitPadWords + kSplitLoadWords;
-constexpr uint32_t kSplitLoadsPerLane = (kSplitLoadWords / 4 + kSplitThreads - 1) / kSplitThreads;
-constexpr uint32_t kSplitQOff = kSplitPadWords * 32 - 1;      // LDS bit of stream bit 0, minus one
-constexpr uint32_t kSplitMaxChunks = kSplitSyms >> 8;         // chunks per workgroup at C = 256
 constexpr uint32_t kSplitWarmBits = 512;                      // walked before a piece, not counted
 
+// 2^kL codes per lane.
+template <int kL>
+struct SplitShape {
+  static constexpr uint32_t kLog2Syms = kL + 8;               // symbols per workgroup
+  static constexpr uint32_t kSyms = 1u << kLog2Syms;
+  static constexpr uint32_t kCapBits = kSyms * kMaxCodeBits + 128;  // + alignment of the base
+  static constexpr uint32_t kLoadWords = ((kCapBits + 31) / 32 + 4 + 3) & ~3u;
+  static constexpr uint32_t kLoadsPerLane = (kLoadWords / 4 + kSplitThreads - 1) / kSplitThreads;
+  static constexpr uint32_t kMaxChunks = kSyms >> 8;          // chunks per workgroup at C = 256
+};
+
+template <int kL>
 struct SplitSmem {
+  using Sh = SplitShape<kL>;
   uint16_t lut[2048];
-  uint32_t span[kSplitSpanWords];         // stream words from base_bit on (memory byte order)
-  uint8_t out[kSplitSyms];                // decoded symbols, one per byte
+  // stream words from base_bit on, most-significant-first
+  __attribute__((aligned(16))) uint32_t span[kSplitPadWords + Sh::kLoadWords];
+  __attribute__((aligned(16))) uint8_t out[Sh::kSyms];        // decoded symbols, one per byte
   uint32_t xs[2][kSplitThreads];          // walk exits, by round parity
   uint32_t excl[kSplitThreads];           // exclusive scan of the code counts
   uint32_t wsum[kSplitThreads / 64];
-  uint32_t chunk_bad[kSplitMaxChunks];
+  uint32_t chunk_bad[Sh::kMaxChunks];
   uint32_t any[3];                        // correction rounds: some exit changed
 };
+static_assert(kSplitUnitLog2 == SplitShape<6>::kLog2Syms, "the batched form's units");
+static_assert(sizeof(SplitSmem<6>) * 3 <= 160 * 1024, "three workgroups per CU");
 
-static_assert(offsetof(SplitSmem, span) % 16 == 0 && offsetof(SplitSmem, out) % 16 == 0,
-              "16-byte LDS accesses");
-static_assert(sizeof(SplitSmem) * 3 <= 160 * 1024, "three workgroups per CU");
-
-// Length of the code starting at stream bit `rel` (relative to the copy).
-__device__ __forceinline__ uint32_t split_code_len(const uint32_t* span, uint32_t rel,
-                                                   uint32_t sh_lo, uint32_t sh_hi) {
-  const uint32_t q = rel + kSplitQOff;
-  const uint32_t w0 = __builtin_bswap32(span[q >> 5]), w1 = __builtin_bswap32(span[(q >> 5) + 1]);
-  const uint32_t A = __builtin_amdgcn_alignbit(w0, w1, ~q);
-  const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, A, 29);
-  return 32u - __builtin_amdgcn_perm(sh_hi, sh_lo, sel);
+// Positions in a split decode are bit addresses in LDS: bit b of the stream's
+// copy, minus one, as 8 * (the copy's byte address) + b - 1, so that the word
+// that holds a position is (x >> 3) & ~3 and its shift the low five bits.
+typedef __attribute__((address_space(3))) uint32_t LdsWord;
+__device__ __forceinline__ const LdsWord* split_word(uint32_t x) {
+  return (const LdsWord*)(uintptr_t)((x >> 3) & ~3u);
 }
 
-// The four words holding stream bits rel .. rel + 95, most-significant-first
-// (and q for the chain).
-__device__ __forceinline__ Window split_window(const uint32_t* span, uint32_t rel, uint32_t& q) {
-  q = rel + kSplitQOff;
-  const uint32_t* rr = span + (q >> 5);
+// The four words holding 96 bits from x on, most-significant-first.
+__device__ __forceinline__ Window split_window(uint32_t x) {
+  const LdsWord* rr = split_word(x);
   Window w;
-  w.w0 = __builtin_bswap32(rr[0]);
-  w.w1 = __builtin_bswap32(rr[1]);
-  w.w2 = __builtin_bswap32(rr[2]);
-  w.w3 = __builtin_bswap32(rr[3]);
+  w.w0 = rr[0];
+  w.w1 = rr[1];
+  w.w2 = rr[2];
+  w.w3 = rr[3];
   return w;
 }
 
 // Walk code lengths from x while x < end: returns the first code start at
-// or past end and adds the codes passed to cnt.
-__device__ __forceinline__ uint32_t split_walk(const uint32_t* span, uint32_t x, uint32_t end,
-                                               uint32_t sh_lo, uint32_t sh_hi, uint32_t& cnt) {
-  while (x < end) {
-    uint32_t q;
-    const Window W = split_window(span, x, q);
-    uint32_t A = __builtin_amdgcn_alignbit(W.w0, W.w1, ~q);
-    uint32_t B = __builtin_amdgcn_alignbit(W.w1, W.w2, ~q);
-    uint32_t Cw = __builtin_amdgcn_alignbit(W.w2, W.w3, ~q);
+// or past end and adds the codes passed to cnt.  Eight codes per window, on
+// a 64-bit register of the stream shifted left by each length (ln_lo, ln_hi:
+// the lengths by area code) and filled up once in between: four
+// instructions per code.  Windows that cannot reach the end (88 bits) count
+// eight codes unseen; the last ones note every code's end (t, relative to x)
+// and take the first at or past it.
+struct SplitBits {
+  uint64_t W;   // 64 bits of the stream from the current code on
+  uint32_t C;   // ... and the next 32
+  __device__ __forceinline__ explicit SplitBits(uint32_t x) {
+    const Window w = split_window(x);
+    W = ((uint64_t)__builtin_amdgcn_alignbit(w.w0, w.w1, ~x) << 32) |
+        __builtin_amdgcn_alignbit(w.w1, w.w2, ~x);
+    C = __builtin_amdgcn_alignbit(w.w2, w.w3, ~x);
+  }
+  __device__ __forceinline__ void skip(uint32_t len) { W <<= len & 63u; }
+  __device__ __forceinline__ void fill(uint32_t t) {  // t = 1 .. 44 bits skipped
+    W |= ((uint64_t)C << 32) >> ((0u - t) & 63u);
+  }
+};
+__device__ __forceinline__ uint32_t split_walk(uint32_t x, uint32_t end, uint32_t ln_lo,
+                                               uint32_t ln_hi, uint32_t& cnt) {
+  while ((int32_t)(end - x) > (int32_t)(8 * kMaxCodeBits)) {
+    SplitBits B(x);
+    uint32_t t = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {  // at most 88 of the window's 96 bits
-      const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, A, 29);
-      const uint32_t sft = __builtin_amdgcn_perm(sh_hi, sh_lo, sel);
-      const bool act = x < end;  // once past the end, x stays there
-      x += act ? 32u - sft : 0u;
-      cnt += act ? 1u : 0u;
-      A = __builtin_amdgcn_alignbit(A, B, sft);
-      B = __builtin_amdgcn_alignbit(B, Cw, sft);
-      Cw = __builtin_amdgcn_alignbit(Cw, 0u, sft);
+    for (int k = 0; k < 8; ++k) {
+      // (bytes above the lowest are area 0's: ignored by the shifts)
+      const uint32_t len = __builtin_amdgcn_perm(ln_hi, ln_lo, (uint32_t)(B.W >> 61));
+      B.skip(len);
+      t += len;
+      if (k == 3) B.fill(t);
     }
+    x += t & 0xFFu;
+    cnt += 8;
+  }
+  while (x < end) {
+    SplitBits B(x);
+    const uint32_t rem = end - x;
+    uint32_t t = 0, past = ~0u, c = 0;  // past: least t - rem without a borrow
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t sel = __builtin_amdgcn_alignbit(kAreaSel, (uint32_t)(B.W >> 32), 29);
+      const uint32_t len = __builtin_amdgcn_perm(ln_hi, ln_lo, sel);
+      c += (t - rem) >> 31;
+      B.skip(len);
+      t += len;
+      past = min(past, t - rem);
+      if (k == 3) B.fill(t);
+    }
+    cnt += c;
+    x = (past >> 31) ? x + t : end + past;
   }
   return x;
-}
-
-// gcd of the code lengths of the areas that hold symbols: the largest k
-// that divides every length (lengths are at most kMaxCodeBits).
-__device__ __forceinline__ uint32_t code_length_gcd(const qlc_table* __restrict__ table) {
-  const AreaFields A = read_areas(table);
-  uint32_t lens = 0;  // bit L set: some area has codes of length L
-#pragma unroll
-  for (uint32_t a = 0; a < 8; ++a)
-    if (a < A.na && A.cnt[a] != 0) lens |= 1u << (A.p + A.w[a]);
-  uint32_t d = 1;
-#pragma unroll
-  for (uint32_t k = 2; k <= kMaxCodeBits; ++k) {
-    uint32_t mult = 0;
-#pragma unroll
-    for (uint32_t m = k; m <= kMaxCodeBits; m += k) mult |= 1u << m;
-    if (lens != 0 && (lens & ~mult) == 0) d = k;
-  }
-  return d;
 }
 
 // The LUT of a split decode and what the walks need from the table.
@@ -1853,19 +1910,20 @@ struct SplitLut {
   bool ok;                // the table codes this alphabet
 };
 
-// Decode split unit `unit` (symbols unit * 16384 onwards) of an n-symbol
+// Decode split unit `unit` (symbols unit << Sh::kLog2Syms onwards) of an n-symbol
 // stream with all 256 threads of the block (tid = threadIdx.x).  With
 // `table` given, the LUT is built into S.lut and L set (while the stream's
 // loads are in flight); with table == nullptr, S.lut and L hold a LUT built
 // before.  Stores the unit's symbols; returns true in the lanes of a corrupt
 // chunk.  Nothing is decoded or stored if L.ok is false.
-template <int kBits>
+template <int kBits, int kL>
 __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, uint64_t total,
                                             const uint64_t* __restrict__ index_p,
                                             uint32_t log2_chunk, uint64_t n,
                                             uint8_t* __restrict__ out_p, uint64_t unit,
                                             const qlc_table* __restrict__ table, SplitLut& L,
-                                            SplitSmem& S, uint32_t tid) {
+                                            SplitSmem<kL>& S, uint32_t tid) {
+  using Sh = SplitShape<kL>;
   const QLC_GLOBAL uint64_t* __restrict__ index = (const QLC_GLOBAL uint64_t*)index_p;
   // a table to build the LUT from: its copy goes to the output buffer
   // (free until the decode); its load is issued first and written after the
@@ -1875,15 +1933,15 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
   const uint4 tv = tab_lane ? ((const uint4*)table)[tid] : make_uint4(0, 0, 0, 0);
   if (tid < kSplitPadWords) S.span[tid] = 0;
   if (tid < 3) S.any[tid] = 0;
-  if (tid < kSplitMaxChunks) S.chunk_bad[tid] = 0;
+  if (tid < Sh::kMaxChunks) S.chunk_bad[tid] = 0;
 
   const uint32_t C = 1u << log2_chunk;
-  const uint32_t log2_g = log2_chunk - 6;                 // G = C / 64 lanes per chunk
+  const uint32_t log2_g = log2_chunk - kL;                // G = C / 2^kL lanes per chunk
   const uint32_t G = 1u << log2_g;
   const uint32_t g = tid & (G - 1);
   const uint32_t slot = tid >> log2_g;                    // chunk slot in the workgroup
   const uint64_t nchunks = (n + C - 1) >> log2_chunk;
-  const uint64_t j0 = unit << (kSplitLog2Syms - log2_chunk);
+  const uint64_t j0 = unit << (Sh::kLog2Syms - log2_chunk);
   const uint64_t j = j0 + slot;
   // this lane's index entries, loaded with the span's
   uint64_t s_abs = 0, e_abs = 0;
@@ -1897,18 +1955,18 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
   if (j0 < nchunks) {
     const uint64_t s0 = index[j0];
     base_bit = (((s0 < total ? s0 : total) >> 3) & ~15ull) << 3;
-    const uint64_t jl = (j0 + (kSplitSyms >> log2_chunk) < nchunks ? j0 + (kSplitSyms >> log2_chunk)
+    const uint64_t jl = (j0 + (Sh::kSyms >> log2_chunk) < nchunks ? j0 + (Sh::kSyms >> log2_chunk)
                                                                   : nchunks) - 1;
     hi = jl + 1 < nchunks ? index[jl + 1] : total;
     if (hi < base_bit) hi = base_bit;
-    if (hi - base_bit > kSplitCapBits) hi = base_bit + kSplitCapBits;
+    if (hi - base_bit > Sh::kCapBits) hi = base_bit + Sh::kCapBits;
   }
   // the table's copy first, then the stream's loads, which stay in flight
   // while the LUT is built
   if (tab_lane) ((uint4*)tl)[tid] = tv;
   const uint32_t nvec =
       j0 < nchunks ? (uint32_t)((((hi - base_bit + 31) >> 5) + 4 + 3) >> 2) : 0u;
-  uint4 sv[kSplitLoadsPerLane];
+  uint4 sv[Sh::kLoadsPerLane];
   {
     const uint64_t stream_bytes = ((total + 31) >> 5) << 2;
     const uint64_t base_byte = base_bit >> 3;
@@ -1918,23 +1976,25 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
         (void*)(bits + (base_byte < stream_bytes ? base_byte : 0)), (short)0, (int)(uint32_t)avail,
         0x00020000);
 #pragma unroll
-    for (uint32_t k = 0; k < kSplitLoadsPerLane; ++k) {
+    for (uint32_t k = 0; k < Sh::kLoadsPerLane; ++k) {
       const uint32_t i = tid + k * kSplitThreads;
       sv[k] = bufload16(rsrc, i < nvec ? i * 16 : kOobOffset);
     }
   }
   lds_barrier();
   if (table != nullptr) {
-    build_dec_lut(tl, S.lut, L.sh_lo, L.sh_hi);
+    build_dec_lut(tl, S.lut, L.sh_lo, L.sh_hi, L.d);
     L.ok = mode_symbol_bits(tl->mode) == kBits;
-    L.d = code_length_gcd(tl);
   }
   const uint32_t sh_lo = L.sh_lo, sh_hi = L.sh_hi, d = L.d;
   const bool table_ok = L.ok;
 #pragma unroll
-  for (uint32_t k = 0; k < kSplitLoadsPerLane; ++k) {
+  for (uint32_t k = 0; k < Sh::kLoadsPerLane; ++k) {
     const uint32_t i = tid + k * kSplitThreads;
-    if (i < nvec) *(uint4*)&S.span[kSplitPadWords + 4 * i] = sv[k];
+    if (i < nvec)
+      *(uint4*)&S.span[kSplitPadWords + 4 * i] =
+          make_uint4(__builtin_bswap32(sv[k].x), __builtin_bswap32(sv[k].y),
+                     __builtin_bswap32(sv[k].z), __builtin_bswap32(sv[k].w));
   }
   lds_barrier();
 
@@ -1946,10 +2006,11 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
     const uint64_t left = n - (j << log2_chunk);
     nsym = (uint32_t)(left < C ? left : C);
     live = s <= e && e <= total && (j != 0 || s == 0) && s >= base_bit &&
-           e - base_bit <= kSplitCapBits && e - s <= (uint64_t)nsym * kMaxCodeBits;
+           e - base_bit <= Sh::kCapBits && e - s <= (uint64_t)nsym * kMaxCodeBits;
     if (live) {
-      s_rel = (uint32_t)(s - base_bit);
-      e_rel = (uint32_t)(e - base_bit);
+      const uint32_t at = 8u * (uint32_t)(uintptr_t)(LdsWord*)&S.span[kSplitPadWords] - 1u;
+      s_rel = at + (uint32_t)(s - base_bit);
+      e_rel = at + (uint32_t)(e - base_bit);
       const uint32_t len = e_rel - s_rel;
       const uint32_t piece = (len + G - 1) >> log2_g;
       const uint32_t a = min(g * piece, len), b = min((g + 1) * piece, len);
@@ -1968,10 +2029,12 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
 
   // ---- phase 1: length walks from the guessed starts ----
   uint32_t start = 0, cnt = 0, x = 0;
-  if (live) {
+  const uint32_t ln_lo = 0x20202020u - sh_lo, ln_hi = 0x20202020u - sh_hi;
+  {
+    // (lanes without a piece walk nothing)
     uint32_t warm = 0;
-    start = split_walk(S.span, lo, piece_lo, sh_lo, sh_hi, warm);  // first start in the piece
-    x = split_walk(S.span, start, end, sh_lo, sh_hi, cnt);
+    start = split_walk(lo, piece_lo, ln_lo, ln_hi, warm);  // first start in the piece
+    x = split_walk(start, end, ln_lo, ln_hi, cnt);
   }
 
   // ---- phase 2: correction rounds ----
@@ -1981,26 +2044,9 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
     const uint32_t prev = g == 0 ? s_rel : S.xs[r & 1][tid - 1];
     bool changed = false;
     if (live && g != 0 && prev != start) {
-      // new path from prev, old path from start, in step until they meet
-      uint32_t a = prev, b = start, ca = 0, cb = 0;
-      bool met = false;
-      for (;;) {
-        if (a == b) {
-          met = true;
-          break;
-        }
-        if (a < b) {
-          if (a >= end) break;
-          a += split_code_len(S.span, a, sh_lo, sh_hi);
-          ++ca;
-        } else {
-          if (b >= end) break;
-          b += split_code_len(S.span, b, sh_lo, sh_hi);
-          ++cb;
-        }
-      }
-      const uint32_t nx = met ? x : a;
-      cnt = met ? cnt - cb + ca : ca;
+      // the piece again, from prev
+      cnt = 0;
+      const uint32_t nx = split_walk(prev, end, ln_lo, ln_hi, cnt);
       changed = nx != x;
       x = nx;
       start = prev;
@@ -2016,12 +2062,7 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
 
   // ---- phase 3: first symbol of each lane (scan of the counts) ----
   const uint32_t lane = tid & 63, wave = tid >> 6;
-  uint32_t incl = cnt;
-#pragma unroll
-  for (int k = 1; k < 64; k <<= 1) {
-    const uint32_t y = __shfl_up(incl, k, 64);
-    if (lane >= (uint32_t)k) incl += y;
-  }
+  uint32_t incl = wave_inclusive_scan_u32(cnt);
   if (lane == 63) S.wsum[wave] = incl;
   lds_barrier();
   for (uint32_t w = 0; w < wave; ++w) incl += S.wsum[w];
@@ -2035,42 +2076,45 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
   // ---- phase 4: decode into the LDS copy of the output ----
   if (live && !bad) {
     uint8_t* dst = S.out + (slot << log2_chunk) + (incl - cnt - cbase);
-    uint32_t pos = start, errbits = 0, q;
-    Window W = split_window(S.span, pos, q);
+    uint32_t pos = start, errbits = 0;
+    Window W = split_window(pos);
     const uint32_t full = cnt >> 3, rem = cnt & 7u;
     for (uint32_t k0 = 0; k0 < full; ++k0, dst += 8) {
       uint32_t c[8], e[8];
-      pos += decode_chain(W, q, sh_lo, sh_hi, c);
-      W = split_window(S.span, pos, q);  // the next group's window, read early
+      pos += decode_chain(W, pos, sh_lo, sh_hi, c);
+      W = split_window(pos);  // the next group's window, read early
 #pragma unroll
       for (uint32_t k = 0; k < 8; ++k) e[k] = S.lut[c[k]];
-#pragma unroll
-      for (uint32_t k = 0; k < 8; ++k) {
-        dst[k] = (uint8_t)e[k];
-        errbits |= e[k];
-      }
+      const uint2 r = pack_group<8>(e, errbits);
+      __builtin_memcpy(dst, &r, 8);
     }
     if (rem) {
       uint32_t c[8], e[8];
-      decode_chain(W, q, sh_lo, sh_hi, c);
+      decode_chain(W, pos, sh_lo, sh_hi, c);
 #pragma unroll
-      for (uint32_t k = 0; k < 7; ++k) e[k] = S.lut[c[k]];
-#pragma unroll
-      for (uint32_t k = 0; k < 7; ++k) {
-        if (k < rem) {
-          dst[k] = (uint8_t)e[k];
-          errbits |= e[k];
-        }
+      for (uint32_t k = 0; k < 8; ++k) e[k] = k < rem ? S.lut[c[k]] : 0u;
+      uint2 r = pack_group<8>(e, errbits);
+      if (rem & 4u) {
+        __builtin_memcpy(dst, &r.x, 4);
+        dst += 4;
+        r.x = r.y;
       }
+      if (rem & 2u) {
+        const uint16_t h = (uint16_t)r.x;
+        __builtin_memcpy(dst, &h, 2);
+        dst += 2;
+        r.x >>= 16;
+      }
+      if (rem & 1u) *dst = (uint8_t)r.x;
     }
-    bad = (errbits & kBadMask) != 0;
+    bad = (errbits & bad_mask<8>()) != 0;
   }
   lds_barrier();
 
   // ---- the workgroup's output, coalesced ----
-  const uint64_t sym0 = unit << kSplitLog2Syms;
+  const uint64_t sym0 = unit << Sh::kLog2Syms;
   if (table_ok && sym0 < n) {
-    const uint32_t nsw = (uint32_t)(n - sym0 < kSplitSyms ? n - sym0 : kSplitSyms);
+    const uint32_t nsw = (uint32_t)(n - sym0 < Sh::kSyms ? n - sym0 : Sh::kSyms);
     QLC_GLOBAL uint8_t* o = (QLC_GLOBAL uint8_t*)out_p + ((sym0 * kBits) >> 3);
     if (kBits == 8) {
       for (uint32_t i = tid; i < (nsw >> 4); i += kSplitThreads) {
@@ -2100,16 +2144,16 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
   return bad;
 }
 
-template <int kBits>
+template <int kBits, int kL>
 __global__ __launch_bounds__(kSplitThreads) void k_decode_split(
     const uint8_t* __restrict__ bits, const uint64_t* __restrict__ total_p,
     const uint64_t* __restrict__ index_p, uint32_t log2_chunk,
     const qlc_table* __restrict__ table, uint64_t n, uint8_t* __restrict__ out_p,
     uint32_t* __restrict__ err_out, WsHeader* __restrict__ hdr) {
-  __shared__ SplitSmem S;
+  __shared__ SplitSmem<kL> S;
   const uint32_t tid = threadIdx.x;
   SplitLut L;
-  const bool bad = split_block<kBits>(bits, *total_p, index_p, log2_chunk, n, out_p, blockIdx.x,
+  const bool bad = split_block<kBits, kL>(bits, *total_p, index_p, log2_chunk, n, out_p, blockIdx.x,
                                       table, L, S, tid);
   set_error_wave(&hdr->dec_err, QLC_ERR_CORRUPT_STREAM, bad);
   if (!L.ok && tid == 0) set_error(&hdr->dec_err, QLC_ERR_INVALID_ARGUMENT);
@@ -2229,7 +2273,7 @@ __global__ __launch_bounds__(kPlanThreads) void k_batch_plan(
         const uint32_t l2c = log2_unit - kDecThreadsLog2;
         const uint64_t chunks = (jb.n + (1ull << l2c) - 1) >> l2c;
         split = decode && (decode_split == 2 || (decode_split == 1 && chunks < kDecThreads));
-        const uint32_t lu = split ? kSplitLog2Syms : log2_unit;
+        const uint32_t lu = split ? kSplitUnitLog2 : log2_unit;
         const uint64_t u = (jb.n + (1ull << lu) - 1) >> lu;
         cnt = (uint32_t)(decode ? u : (u ? u : 1));
         *jb.err = 0;
@@ -2437,11 +2481,11 @@ __global__ __launch_bounds__(kEncThreads, 4) void k_encode_batched(
 // is rebuilt only when the job changes.
 union BatchDecSmem {
   DecSmem lane;
-  SplitSmem split;
+  SplitSmem<6> split;
 };
-static_assert(offsetof(DecSmem, lut) == 0 && offsetof(SplitSmem, lut) == 0, "shared LUT");
+static_assert(offsetof(DecSmem, lut) == 0 && offsetof(SplitSmem<6>, lut) == 0, "shared LUT");
 static_assert(kSplitThreads == kDecThreads, "one block size");
-static_assert(sizeof(SplitSmem) <= offsetof(DecSmem, ring) + 4 * kStageBase, "the ticket's word");
+static_assert(sizeof(SplitSmem<6>) <= offsetof(DecSmem, ring) + 4 * kStageBase, "the ticket's word");
 
 template <int kBits>
 __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
@@ -2467,9 +2511,8 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
       qlc_table* tl = (qlc_table*)S.lane.ring;  // free between work items
       table_to_lds(jb.table, tl, tid);
       __syncthreads();
-      build_dec_lut(tl, S.lane.lut, L.sh_lo, L.sh_hi);
+      build_dec_lut(tl, S.lane.lut, L.sh_lo, L.sh_hi, L.d);
       L.ok = mode_symbol_bits(tl->mode) == kBits;
-      L.d = code_length_gcd(tl);
       __syncthreads();
       cur = k;
     }
@@ -2477,7 +2520,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
       const uint32_t unit = p - js[k].base;
       const bool bad =
           __builtin_amdgcn_readfirstlane(js[k].split)
-              ? split_block<kBits>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
+              ? split_block<kBits, 6>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                    jb.out, unit, nullptr, L, S.split, opaque_tid())
               : decode_block<kBits>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                     jb.out, unit, L.sh_lo, L.sh_hi, S.lane, opaque_tid(), false);
@@ -2576,15 +2619,36 @@ hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const ui
   return hipGetLastError();
 }
 
+// log2 of the codes per lane.  32 instead of 64 shorten a lane's walk and
+// decode where the workgroups do not fill the device anyway (1 Mi symbols at
+// C = 2048: 10.1 against 10.6-13.2 us; equal at 2 Mi); beyond, the 512-bit
+// warm-up of twice as many lanes costs more (4 Mi: 15.1 against 13.8 us,
+// 64 Mi: 107 against 73 us).  A unit of 256 lanes holds whole chunks.
+static uint32_t split_codes_log2(uint64_t n, uint32_t log2_chunk) {
+  return n <= (2ull << 20) && log2_chunk <= SplitShape<5>::kLog2Syms ? 5u : 6u;
+}
+
 hipError_t launch_decode_split(const uint8_t* bits_in, const uint64_t* total, const uint64_t* index,
                                uint32_t log2_chunk, const qlc_table* table, uint64_t n,
                                uint32_t bits, uint8_t* out, uint32_t* err_out, WsHeader* hdr,
                                hipStream_t stream) {
   if (log2_chunk < 8 || log2_chunk > kSplitMaxLog2Chunk) return hipErrorInvalidValue;
-  uint64_t blocks = (n + kSplitSyms - 1) >> kSplitLog2Syms;
+  const uint32_t l = split_codes_log2(n, log2_chunk);
+  uint64_t blocks = (n + (256ull << l) - 1) >> (l + 8);
   if (blocks < 1) blocks = 1;
-  QLC_LAUNCH_BITS(bits, k_decode_split, dim3((uint32_t)blocks), dim3(kSplitThreads), bits_in,
-                  total, index, log2_chunk, table, n, out, err_out, hdr);
+#define QLC_LAUNCH_SPLIT(B, L)                                                                    \
+  hipLaunchKernelGGL((k_decode_split<B, L>), dim3((uint32_t)blocks), dim3(kSplitThreads), 0,      \
+                     stream, bits_in, total, index, log2_chunk, table, n, out, err_out, hdr)
+  if (l == 5) {
+    if (bits == 4) QLC_LAUNCH_SPLIT(4, 5);
+    else if (bits == 6) QLC_LAUNCH_SPLIT(6, 5);
+    else QLC_LAUNCH_SPLIT(8, 5);
+  } else {
+    if (bits == 4) QLC_LAUNCH_SPLIT(4, 6);
+    else if (bits == 6) QLC_LAUNCH_SPLIT(6, 6);
+    else QLC_LAUNCH_SPLIT(8, 6);
+  }
+#undef QLC_LAUNCH_SPLIT
   return hipGetLastError();
 }
 
