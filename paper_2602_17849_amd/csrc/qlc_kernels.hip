@@ -977,11 +977,16 @@ __global__ __launch_bounds__(kHistThreads) void k_segment_bits(
   const uint64_t seg1 = (seg0 + (1ull << log2_seg)) < n ? seg0 + (1ull << log2_seg) : n;
   const uint64_t v0 = seg0 >> 4, v1 = seg1 >> 4;  // whole 16-symbol groups
   uint32_t s = 0;
+  // from the segment's end to its start: what is read last is what the
+  // encoder reads first, while the memory-side cache still holds it (48 Mi
+  // symbols 37.2 -> 36.2 us, 2^28 163.6 -> 156.0; the histogram pass, read so,
+  // gained 1 % at 2^28 and lost 1 % below 16 Mi, and keeps its order)
+  const uint64_t rev = v0 + v1 - 1;
   uint64_t i = v0 + tid;
   for (; i + 3 * kHistThreads < v1; i += 4 * kHistThreads) {
-    const uint4 a = SI::fetch16(in, i << 4), b = SI::fetch16(in, (i + kHistThreads) << 4);
-    const uint4 c = SI::fetch16(in, (i + 2 * kHistThreads) << 4);
-    const uint4 d = SI::fetch16(in, (i + 3 * kHistThreads) << 4);
+    const uint4 a = SI::fetch16(in, (rev - i) << 4), b = SI::fetch16(in, (rev - (i + kHistThreads)) << 4);
+    const uint4 c = SI::fetch16(in, (rev - (i + 2 * kHistThreads)) << 4);
+    const uint4 d = SI::fetch16(in, (rev - (i + 3 * kHistThreads)) << 4);
     const uint32_t w[16] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w,
                             c.x, c.y, c.z, c.w, d.x, d.y, d.z, d.w};
 #pragma unroll
@@ -990,7 +995,7 @@ __global__ __launch_bounds__(kHistThreads) void k_segment_bits(
            len[w[k] >> 24];
   }
   for (; i < v1; i += kHistThreads) {
-    const uint4 a = SI::fetch16(in, i << 4);
+    const uint4 a = SI::fetch16(in, (rev - i) << 4);
     const uint32_t w[4] = {a.x, a.y, a.z, a.w};
 #pragma unroll
     for (int k = 0; k < 4; ++k)
