@@ -7,6 +7,7 @@
 
 #include "qlc_device.h"
 #include "qlc_kernels.h"
+#include "qlc_lane_pos.h"
 
 namespace qlc {
 
@@ -1149,14 +1150,7 @@ __global__ __launch_bounds__(kEncThreads) void k_encode(
 // SIMD (32 Mi 6-bit symbols, C = 1024) 47.9 -> 46.5 us.
 // ===========================================================================
 constexpr int kDecLanes = kDecThreads;     // chunks per workgroup
-constexpr uint32_t kSbLog2Bits = 9;        // superblock: 512 bits = 64 bytes
-constexpr uint32_t kSbBits = 1u << kSbLog2Bits;
-constexpr uint32_t kRingBits = 4 * kSbBits;  // ring of four superblocks
-constexpr int kRingWords = kRingBits / 32 + 3;  // ... and 3 mirror words
-constexpr uint32_t kLookaheadBits = 3 * kSbBits;  // request a superblock up to three ahead
-constexpr uint32_t kReach = 3 * 88 + 128;  // bits past q that four groups' windows may read
-static_assert(kReach + kSbBits <= kLookaheadBits, "a lane can always request what it may need");
-constexpr uint32_t kOobOffset = 0xFFFFF000u;  // (room for the offsets added to it)
+constexpr int kRingWords = kRingBits / 32 + 3;  // the ring and 3 mirror words
 constexpr uint32_t kAreaSel = 0x01818180u;  // alignbit(kAreaSel, A, 29) = (A >> 29) | 0x0C0C0C00
 constexpr uint32_t kStagePairs = 8;        // pairs of 8-symbol groups per output run
 constexpr uint32_t kStageLanes = 16;       // output runs staged at a time
@@ -1234,28 +1228,34 @@ struct Refill {
   }
 };
 
-// Position of a lane in its chunk's stream, relative to the wave's base (a
-// multiple of the ring's size, so that positions are also the ring's).
-struct DecLane {
-  uint32_t q;          // bit of the next symbol, minus one
-  uint32_t F;          // first bit not requested yet (a multiple of kSbBits)
-  uint32_t have;       // first bit that is not in the ring yet
+// A lane's position and the superblocks it has in flight.
+struct DecLane : LanePos {
   uint32_t errbits;
 
-  // This lane's request: the superblock at F if it starts within the
-  // lookahead and before the chunk's end.
-  __device__ __forceinline__ void request(Refill& T, __amdgpu_buffer_rsrc_t rsrc, uint32_t endr,
-                                          uint32_t tid) {
-    const bool need = F < min(q + 1 + kLookaheadBits, endr);
-    T.issue(rsrc, need ? F >> 3 : kOobOffset, ((F & (kRingBits - 1)) >> 5) * kDecLanes + tid, tid);
-    F += need ? kSbBits : 0u;
+  __device__ __forceinline__ void request(Refill& T, __amdgpu_buffer_rsrc_t rsrc, uint32_t tid) {
+    const bool need = wants();
+    T.issue(rsrc, need ? load_offset() : kOobOffset,
+            ((F & (kRingBits - 1)) >> 5) * kDecLanes + tid, tid);
+    requested(need);
   }
   // What was requested last, into the ring.
   __device__ __forceinline__ void arrive(const Refill& T, uint32_t* ring_all) {
     T.put(ring_all);
     __builtin_amdgcn_wave_barrier();
-    have = F;
+    arrived();
   }
+};
+
+// What lane_reach drives: a wave's lanes and their loads.
+struct DecWave {
+  DecLane& L;
+  Refill& T;
+  uint32_t* ring;
+  __amdgpu_buffer_rsrc_t rsrc;
+  uint32_t tid;
+  __device__ __forceinline__ bool any(bool b) const { return __any(b); }
+  __device__ __forceinline__ void arrive() const { L.arrive(T, ring); }
+  __device__ __forceinline__ void request() const { L.request(T, rsrc, tid); }
 };
 
 struct Window {
@@ -1586,8 +1586,8 @@ template <int kBits, bool kPart>
 __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, uint32_t tid,
                                             __amdgpu_buffer_rsrc_t rsrc,
                                             __amdgpu_buffer_rsrc_t orsrc, uint32_t log2_chunk,
-                                            uint32_t endr, uint32_t sh_lo, uint32_t sh_hi,
-                                            uint32_t my_groups, bool balance) {
+                                            uint32_t sh_lo, uint32_t sh_hi, uint32_t my_groups,
+                                            bool balance) {
   constexpr uint32_t R = 2 * kStagePairs;       // groups per batch
   constexpr uint32_t kRuns = 64 / kStagePairs;  // runs per store instruction
   const uint32_t lane = tid & 63u;
@@ -1606,6 +1606,7 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
 
   const uint32_t* ring = S.ring + tid;
   uint4* stage = (uint4*)(S.ring + kStageBase + (tid >> 6) * kStageWords);
+  const DecWave wave{L, T, S.ring, rsrc, tid};
   Window W = window_read(ring, L.q);
 // Group G of the batch into the pair half OUT, with MID before the next
 // window's read.
@@ -1621,17 +1622,11 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
     OUT = pack_group<kBits>(e, kPart ? eb : L.errbits);                          \
     if (kPart) L.errbits |= keep ? eb : 0u;                                      \
   }
-#define QLC_DEC_REACH                                                \
-  while (__any(L.have < min(L.q + kReach, endr))) {                  \
-    L.arrive(T, S.ring);                                             \
-    if (!__any(L.have < min(L.q + kReach, endr))) break;             \
-    L.request(T, rsrc, endr, tid);                                   \
-  }
-#define QLC_DEC_REFILL                                               \
-  {                                                                  \
-    L.arrive(T, S.ring);                                             \
-    QLC_DEC_REACH                                                    \
-    L.request(T, rsrc, endr, tid);                                   \
+#define QLC_DEC_REFILL     \
+  {                        \
+    wave.arrive();         \
+    lane_reach(L, wave);   \
+    wave.request();        \
   }
 #pragma unroll 1
   for (uint32_t g0 = 0; g0 < wave_groups; g0 += R) {
@@ -1651,7 +1646,7 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
       QLC_DEC_GROUP(2 * u + 1, b, {})
       pr[u] = pack_pair<kBits>(a, b);
       QLC_DEC_GROUP(2 * u + 2, a, {})
-      QLC_DEC_GROUP(2 * u + 3, b, QLC_DEC_REACH)
+      QLC_DEC_GROUP(2 * u + 3, b, lane_reach(L, wave))
       pr[u + 1] = pack_pair<kBits>(a, b);
       QLC_DEC_GROUP(2 * u + 4, a, {})
       QLC_DEC_GROUP(2 * u + 5, b, {})
@@ -1690,7 +1685,6 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
   }
 #undef QLC_DEC_GROUP
 #undef QLC_DEC_REFILL
-#undef QLC_DEC_REACH
 }
 
 // Decode chunk group `grp` of an n-symbol stream: chunks kDecThreads*grp
@@ -1743,7 +1737,7 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
       const uint64_t left = n - (j << log2_chunk);
       const uint32_t nsym = (uint32_t)(left < C ? left : C);
       if (pos0 > end || end > total || (j == 0 && pos0 != 0) || pos0 < wave_bit ||
-          ((pos0 >> kSbLog2Bits) - base_sb) > (kOobOffset >> (kSbLog2Bits - 3)) - 4096) {
+          ((pos0 >> kSbLog2Bits) - base_sb) > kMaxLaneSb) {
         bad = true;
       } else {
         my_groups = nsym >> 3;
@@ -1751,13 +1745,10 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
       }
     }
     const bool live = (j < nchunks) && !bad;
-    const uint64_t rel0 = base_sb << kSbLog2Bits;  // positions below are relative to it
-    const uint32_t prel = live ? (uint32_t)(pos0 - rel0) : 0u;
-    const uint32_t endr = live ? (uint32_t)(end - rel0) : 0u;  // nothing loaded past the chunk
+    const uint64_t rel0 = base_sb << kSbLog2Bits;  // the wave's base
     DecLane L;
     L.errbits = 0;
-    L.q = prel - 1;
-    L.F = prel & ~(kSbBits - 1);
+    L.start(live, rel0, pos0, end);
     // the first two superblocks (past the chunk's end or the stream's: never
     // needed, or zeros), which reach beyond the first four groups, and the
     // request of the third
@@ -1766,12 +1757,12 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
       Refill U[2];
 #pragma unroll
       for (int s = 0; s < 2; ++s) {
-        U[s].issue(rsrc, live ? L.F >> 3 : kOobOffset,
+        U[s].issue(rsrc, live ? L.load_offset() : kOobOffset,
                    ((L.F & (kRingBits - 1)) >> 5) * kDecLanes + tid, tid);
-        L.F += kSbBits;
+        L.requested(true);
       }
-      L.have = L.F;
-      L.request(T, rsrc, endr, tid);
+      L.arrived();
+      L.request(T, rsrc, tid);
       U[0].put(S.ring);
       U[1].put(S.ring);
     }
@@ -1780,14 +1771,14 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
     // Waves whose 64 chunks are all whole and valid are all but at most the
     // last of a valid stream.
     if (__all(live && my_groups == (C >> 3)))
-      decode_wave<kBits, false>(L, T, S, tid, rsrc, orsrc, log2_chunk, endr, sh_lo, sh_hi,
+      decode_wave<kBits, false>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
                                 my_groups, balance);
     else
-      decode_wave<kBits, true>(L, T, S, tid, rsrc, orsrc, log2_chunk, endr, sh_lo, sh_hi,
+      decode_wave<kBits, true>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
                                my_groups, balance);
     L.arrive(T, S.ring);
     // the position, in 64 bits (a lane that decoded no group is where it began)
-    uint64_t pos = my_groups ? rel0 + L.q + 1 : pos0;
+    uint64_t pos = my_groups ? L.base(rel0) + L.q + 1 : pos0;
     if (live && rem) {  // final partial group of the last chunk
       const Window W = window_read(S.ring + tid, L.q);
       uint32_t A = __builtin_amdgcn_alignbit(W.w0, W.w1, ~L.q);
