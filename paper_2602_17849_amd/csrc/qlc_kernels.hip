@@ -1464,9 +1464,13 @@ __device__ __forceinline__ AreaFields read_areas(const qlc_table* __restrict__ t
 // eight lanes), one area each; done area by area in every lane this took
 // 600 instructions, 1.5 us of a lone wave, before a decode could begin.
 // d: the gcd of the code lengths of the areas that hold symbols.
+// A symbol keeps its low kBits bits (a table made by hand may name others),
+// so that packing need not mask what it ORs together.
+template <int kBits>
 __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ table, uint16_t* lut,
                                               uint32_t& sh_lo, uint32_t& sh_hi, uint32_t& d) {
   const uint32_t tid = threadIdx.x;
+  constexpr uint32_t kSymMask = (1u << kBits) - 1;
   // every entry invalid: 256 threads, 16 bytes each
   constexpr uint32_t kBad2 = kBadEntry | (kBadEntry << 16);
   ((uint4*)lut)[tid] = make_uint4(kBad2, kBad2, kBad2, kBad2);
@@ -1528,7 +1532,7 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
     const uint32_t wa = min((uint32_t)table->width[a], 8u);
     const uint32_t suffix = tid - table->offset[a];
     if (tid < f && suffix < (1u << wa))
-      lut[(a << wa) + suffix] = (uint16_t)table->rank_to_sym[tid];
+      lut[(a << wa) + suffix] = (uint16_t)(table->rank_to_sym[tid] & kSymMask);
   } else {
     // Any other table: per entry, the last area whose range holds the code
     // and whose rank is valid.
@@ -1541,7 +1545,7 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
         if (c >= lo && c < lo + (1u << A.w[k])) {
           const uint32_t rank = A.off[k] + (c - lo);
           if (rank >= A.first[k] && rank < A.first[k] + A.cnt[k] && rank < 256)
-            e = table->rank_to_sym[rank];
+            e = table->rank_to_sym[rank] & kSymMask;
         }
       }
       lut[c] = (uint16_t)e;
@@ -1820,7 +1824,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
   qlc_table* tl = (qlc_table*)S.ring;  // the ring is free until the decode starts
   table_to_lds(table, tl, tid);
   __syncthreads();
-  build_dec_lut(tl, S.lut, sh_lo, sh_hi, d);
+  build_dec_lut<kBits>(tl, S.lut, sh_lo, sh_hi, d);
   const bool table_ok = mode_symbol_bits(tl->mode) == kBits;
   __syncthreads();
   // a table of another alphabet is refused (nothing decoded)
@@ -2071,7 +2075,7 @@ __device__ __forceinline__ bool split_block(const uint8_t* __restrict__ bits, ui
   }
   lds_barrier();
   if (table != nullptr) {
-    build_dec_lut(tl, S.lut, L.sh_lo, L.sh_hi, L.d);
+    build_dec_lut<kBits>(tl, S.lut, L.sh_lo, L.sh_hi, L.d);
     L.ok = mode_symbol_bits(tl->mode) == kBits;
   }
   const uint32_t sh_lo = L.sh_lo, sh_hi = L.sh_hi, d = L.d;
@@ -2602,7 +2606,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
       qlc_table* tl = (qlc_table*)S.lane.ring;  // free between work items
       table_to_lds(jb.table, tl, tid);
       __syncthreads();
-      build_dec_lut(tl, S.lane.lut, L.sh_lo, L.sh_hi, L.d);
+      build_dec_lut<kBits>(tl, S.lane.lut, L.sh_lo, L.sh_hi, L.d);
       L.ok = mode_symbol_bits(tl->mode) == kBits;
       __syncthreads();
       cur = k;
