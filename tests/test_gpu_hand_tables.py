@@ -32,3 +32,70 @@ def test_symbols_outside_the_alphabet(bits, A, p, rem, decoder):
     err, out = gpu_decode(stream, total, index, C, to_dev(tab), n, decoder, bits)
     assert err == 0
     assert np.array_equal(out, datagen.pack_symbols(x, bits))
+
+
+def _codes(width, offset, first, count, r2s):
+    """Every code of an 8-area table as (length, word, symbol or None): the
+    area code, its suffix, and the last area whose code range holds the word
+    and whose ranks hold the one that it names."""
+    w = [min(int(v), 8) for v in width]
+    out = []
+    for a in range(8):
+        for suffix in range(1 << w[a]):
+            word, sym = (a << w[a]) + suffix, None
+            for k in range(8):
+                lo = k << w[k]
+                if lo <= word < lo + (1 << w[k]):
+                    r = int(offset[k]) + word - lo
+                    if int(first[k]) <= r < int(first[k]) + int(count[k]) and r < 256:
+                        sym = int(r2s[r])
+            out.append((3 + w[a], word, sym))
+    return out
+
+
+def _uneven_table(kind):
+    """Table 1 with areas that are not back to back; its codes, valid and not."""
+    ot = oracle.build_table(np.arange(256, 0, -1, dtype=np.uint64), qlc.LAYOUT_PAPER_T1)
+    tab = table_from_oracle(ot).cpu().numpy().copy()
+    width, offset = tab[1024:1032], tab[1032:1040]
+    first, count = tab[1040:1056].view(np.uint16), tab[1056:1072].view(np.uint16)
+    if kind == "gap":              # area 2's ranks moved up: a hole before them
+        first[2] += 3
+        offset[2] += 3
+    elif kind == "decreasing":     # area 1 wider than area 2
+        width[1], count[1] = 4, 16
+    else:                          # more ranks than symbols
+        count[7] = 200
+        first[7] = 88
+    codes = _codes(width, offset, first, count, tab[R2S:R2S + 256])
+    return tab, [c for c in codes if c[2] is not None], [c for c in codes if c[2] is None]
+
+
+@pytest.mark.parametrize("invalid", [False, True])
+@pytest.mark.parametrize("kind", ["gap", "decreasing", "sum_over_256"])
+@pytest.mark.parametrize("decoder", [qlc.DECODER_LANE, qlc.DECODER_SPLIT])
+def test_uneven_areas(kind, decoder, invalid):
+    """Streams of codes that the table gives a symbol: every symbol right.
+    With one code that names none in the last but one chunk: the error, and
+    every other chunk as before."""
+    tab, good, none = _uneven_table(kind)
+    C, n = 256, 256 * 68 + 9
+    rng = np.random.default_rng(11)
+    pick = [good[i] for i in rng.integers(0, len(good), n)]
+    assert len({c[2] for c in pick}) > 200            # most of the ranks are met
+    if invalid:
+        pick[67 * C + 100] = none[len(none) // 2]
+    bits, index, pos = [], [], 0
+    for i, (ln, word, _) in enumerate(pick):
+        if i % C == 0:
+            index.append(pos)
+        bits.append([(word >> (ln - 1 - k)) & 1 for k in range(ln)])
+        pos += ln
+    flat = np.array([b for c in bits for b in c], np.uint8)
+    stream = np.packbits(np.concatenate([flat, np.zeros(-pos % 32, np.uint8)]))
+    sym = np.array([0 if c[2] is None else c[2] for c in pick], np.uint8)
+    err, out = gpu_decode(stream, pos, np.array(index), C, to_dev(tab), n, decoder)
+    assert err == (qlc.QLC_ERR_CORRUPT_STREAM if invalid else 0)
+    ok = np.ones(n, bool)
+    ok[67 * C:68 * C] = not invalid
+    assert np.array_equal(out[ok], sym[ok])
