@@ -1332,6 +1332,12 @@ __device__ __forceinline__ uint2 pack_group(const uint32_t (&e)[8], uint32_t& er
     r.x = (((p3 << 8) | p2) << 16) | ((p1 << 8) | p0);
     r.y = 0u;
   }
+  // Packed here and not where the batch is stored: left to itself the
+  // compiler moves all of a batch's packing there, holds the entries until
+  // then, and extends each of them to 32 bits again (240 more instructions
+  // per batch).
+  if (kBits != 8) asm("" : "+v"(r.x));
+  if (kBits == 6) asm("" : "+v"(r.y));
   return r;
 }
 
@@ -1371,45 +1377,58 @@ __device__ __forceinline__ void store_group(QLC_GLOBAL uint8_t* p, uint2 v) {
 }
 
 // Two consecutive groups (from pack_group) in the output format: 16, 8 or 12
-// bytes in the first words of a uint4.
+// bytes.  A type of that many words: staged and stored as four words whatever
+// the alphabet, the unused ones cost moves and LDS writes (2^26 symbols of 4
+// bits, C = 2048: 78 us, with this and the packing in place 70).
 template <int kBits>
-__device__ __forceinline__ uint4 pack_pair(uint2 a, uint2 b) {
-  if (kBits == 8) return make_uint4(a.x, a.y, b.x, b.y);
-  if (kBits == 4) return make_uint4(a.x, b.x, 0u, 0u);
-  return make_uint4((a.y << 24) | a.x, (b.x << 16) | (a.y >> 8), (b.y << 8) | (b.x >> 16), 0u);
-}
-
-// Store a pair's 2 * kBits bytes at byte off + soff (soff wave-uniform) of a
-// buffer resource.
-template <int kBits>
-__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                           uint32_t soff, uint4 v) {
-  if (kBits == 8) {
-    const v4u32 w = {v.x, v.y, v.z, v.w};
-    __builtin_amdgcn_raw_buffer_store_b128(w, rsrc, off, soff, kStream);
-  } else if (kBits == 4) {
-    const v2u32 w = {v.x, v.y};
-    __builtin_amdgcn_raw_buffer_store_b64(w, rsrc, off, soff, kStream);
-  } else {
-    const v3u32 w = {v.x, v.y, v.z};
-    __builtin_amdgcn_raw_buffer_store_b96(w, rsrc, off, soff, kStream);
+struct PairOf;
+template <>
+struct PairOf<8> {
+  typedef v4u32 T;
+  __device__ static __forceinline__ T make(uint2 a, uint2 b) { return T{a.x, a.y, b.x, b.y}; }
+};
+template <>
+struct PairOf<4> {
+  typedef v2u32 T;
+  __device__ static __forceinline__ T make(uint2 a, uint2 b) { return T{a.x, b.x}; }
+};
+template <>
+struct PairOf<6> {
+  typedef v3u32 T;
+  __device__ static __forceinline__ T make(uint2 a, uint2 b) {
+    return T{(a.y << 24) | a.x, (b.x << 16) | (a.y >> 8), (b.y << 8) | (b.x >> 16)};
   }
+};
+
+// Store a pair's 16, 12 or 8 bytes at byte off + soff (soff wave-uniform) of a
+// buffer resource.
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                           uint32_t soff, v4u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, off, soff, kStream);
+}
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                           uint32_t soff, v3u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b96(v, rsrc, off, soff, kStream);
+}
+__device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                           uint32_t soff, v2u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, off, soff, kStream);
 }
 
 // ... and only the first group's kBits bytes.
-template <int kBits>
 __device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
-                                            uint32_t soff, uint4 v) {
-  if (kBits == 8) {
-    const v2u32 w = {v.x, v.y};
-    __builtin_amdgcn_raw_buffer_store_b64(w, rsrc, off, soff, kStream);
-  } else if (kBits == 4) {
-    __builtin_amdgcn_raw_buffer_store_b32(v.x, rsrc, off, soff, kStream);
-  } else {
-    __builtin_amdgcn_raw_buffer_store_b16((short)v.x, rsrc, off, soff, kStream);
-    __builtin_amdgcn_raw_buffer_store_b16((short)(v.x >> 16), rsrc, off + 2, soff, kStream);
-    __builtin_amdgcn_raw_buffer_store_b16((short)v.y, rsrc, off + 4, soff, kStream);
-  }
+                                            uint32_t soff, v4u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b64(v2u32{v.x, v.y}, rsrc, off, soff, kStream);
+}
+__device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                            uint32_t soff, v3u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b16((short)v.x, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b16((short)(v.x >> 16), rsrc, off + 2, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b16((short)v.y, rsrc, off + 4, soff, kStream);
+}
+__device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
+                                            uint32_t soff, v2u32 v) {
+  __builtin_amdgcn_raw_buffer_store_b32(v.x, rsrc, off, soff, kStream);
 }
 
 // Copy a table (device memory, 16-byte aligned) into LDS: one 16-byte load
@@ -1609,7 +1628,8 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
       pm ? (uint32_t)__builtin_amdgcn_readlane((int)my_groups, (int)part_lane) : 0u;
 
   const uint32_t* ring = S.ring + tid;
-  uint4* stage = (uint4*)(S.ring + kStageBase + (tid >> 6) * kStageWords);
+  typedef typename PairOf<kBits>::T Pair;
+  uint32_t* stage = S.ring + kStageBase + (tid >> 6) * kStageWords;
   const DecWave wave{L, T, S.ring, rsrc, tid};
   Window W = window_read(ring, L.q);
 // Group G of the batch into the pair half OUT, with MID before the next
@@ -1642,22 +1662,22 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
         default: __builtin_amdgcn_s_setprio(0); break;
       }
     }
-    uint4 pr[kStagePairs];
+    Pair pr[kStagePairs];
 #pragma unroll
     for (uint32_t u = 0; u < kStagePairs; u += 4) {
       uint2 a, b;
       QLC_DEC_GROUP(2 * u + 0, a, {})
       QLC_DEC_GROUP(2 * u + 1, b, {})
-      pr[u] = pack_pair<kBits>(a, b);
+      pr[u] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 2, a, {})
       QLC_DEC_GROUP(2 * u + 3, b, lane_reach(L, wave))
-      pr[u + 1] = pack_pair<kBits>(a, b);
+      pr[u + 1] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 4, a, {})
       QLC_DEC_GROUP(2 * u + 5, b, {})
-      pr[u + 2] = pack_pair<kBits>(a, b);
+      pr[u + 2] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 6, a, {})
       QLC_DEC_GROUP(2 * u + 7, b, QLC_DEC_REFILL)
-      pr[u + 3] = pack_pair<kBits>(a, b);
+      pr[u + 3] = PairOf<kBits>::make(a, b);
     }
 #pragma unroll
     for (uint32_t h = 0; h < 64 / kStageLanes; ++h) {
@@ -1665,23 +1685,23 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
       if (lane / kStageLanes == h) {
 #pragma unroll
         for (uint32_t p = 0; p < kStagePairs; ++p)
-          stage[(lane % kStageLanes) * (kStageRow / 4) + p] = pr[p];
+          *(Pair*)(stage + (lane % kStageLanes) * kStageRow + p * 4) = pr[p];
       }
       __builtin_amdgcn_wave_barrier();
 #pragma unroll
       for (uint32_t k = 0; k < kStageLanes / kRuns; ++k) {
         const uint32_t c = lane / kStagePairs + kRuns * k;  // chunk of the 16
-        const uint4 v = stage[c * (kStageRow / 4) + part];
+        const Pair v = *(const Pair*)(stage + c * kStageRow + part * 4);
         const uint32_t soff = g0 * kBits + (h * (kStageLanes / kRuns) + k) * run_step;
         if (!kPart) {
-          store_pair<kBits>(orsrc, obase, soff, v);
+          store_pair(orsrc, obase, soff, v);
         } else {
           const uint32_t src = c + kStageLanes * h;
           const uint32_t ngrp = ((full_lanes >> src) & 1u) ? wave_groups
                                 : src == part_lane ? part_groups : 0u;
           const uint32_t ga = g0 + 2 * part;
-          if (ga + 1 < ngrp) store_pair<kBits>(orsrc, obase, soff, v);
-          else if (ga < ngrp) store_first<kBits>(orsrc, obase, soff, v);  // the chunk's last whole group
+          if (ga + 1 < ngrp) store_pair(orsrc, obase, soff, v);
+          else if (ga < ngrp) store_first(orsrc, obase, soff, v);  // the chunk's last whole group
         }
       }
     }
