@@ -1402,33 +1402,39 @@ struct PairOf<6> {
 
 // Store a pair's 16, 12 or 8 bytes at byte off + soff (soff wave-uniform) of a
 // buffer resource.
+template <int kPolicy>
 __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                            uint32_t soff, v4u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, off, soff, kPolicy);
 }
+template <int kPolicy>
 __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                            uint32_t soff, v3u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b96(v, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b96(v, rsrc, off, soff, kPolicy);
 }
+template <int kPolicy>
 __device__ __forceinline__ void store_pair(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                            uint32_t soff, v2u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, off, soff, kPolicy);
 }
 
 // ... and only the first group's kBits bytes.
+template <int kPolicy>
 __device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                             uint32_t soff, v4u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b64(v2u32{v.x, v.y}, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b64(v2u32{v.x, v.y}, rsrc, off, soff, kPolicy);
 }
+template <int kPolicy>
 __device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                             uint32_t soff, v3u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b16((short)v.x, rsrc, off, soff, kStream);
-  __builtin_amdgcn_raw_buffer_store_b16((short)(v.x >> 16), rsrc, off + 2, soff, kStream);
-  __builtin_amdgcn_raw_buffer_store_b16((short)v.y, rsrc, off + 4, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b16((short)v.x, rsrc, off, soff, kPolicy);
+  __builtin_amdgcn_raw_buffer_store_b16((short)(v.x >> 16), rsrc, off + 2, soff, kPolicy);
+  __builtin_amdgcn_raw_buffer_store_b16((short)v.y, rsrc, off + 4, soff, kPolicy);
 }
+template <int kPolicy>
 __device__ __forceinline__ void store_first(__amdgpu_buffer_rsrc_t rsrc, uint32_t off,
                                             uint32_t soff, v2u32 v) {
-  __builtin_amdgcn_raw_buffer_store_b32(v.x, rsrc, off, soff, kStream);
+  __builtin_amdgcn_raw_buffer_store_b32(v.x, rsrc, off, soff, kPolicy);
 }
 
 // Copy a table (device memory, 16-byte aligned) into LDS: one 16-byte load
@@ -1605,7 +1611,10 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
 // half the pair's rate; with a priority that falls with each quarter of the
 // chunk the two end together (256 MiB, C = 2048: 134 -> 130 us; a queue of
 // many groups per workgroup loses 7 % by it).
-template <int kBits, bool kPart>
+//
+// kPolicy: cache policy of the stored runs, kStream but for many 6-bit
+// symbols (stream_six_bit_runs).
+template <int kBits, bool kPart, int kPolicy>
 __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, uint32_t tid,
                                             __amdgpu_buffer_rsrc_t rsrc,
                                             __amdgpu_buffer_rsrc_t orsrc, uint32_t log2_chunk,
@@ -1694,14 +1703,14 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
         const Pair v = *(const Pair*)(stage + c * kStageRow + part * 4);
         const uint32_t soff = g0 * kBits + (h * (kStageLanes / kRuns) + k) * run_step;
         if (!kPart) {
-          store_pair(orsrc, obase, soff, v);
+          store_pair<kPolicy>(orsrc, obase, soff, v);
         } else {
           const uint32_t src = c + kStageLanes * h;
           const uint32_t ngrp = ((full_lanes >> src) & 1u) ? wave_groups
                                 : src == part_lane ? part_groups : 0u;
           const uint32_t ga = g0 + 2 * part;
-          if (ga + 1 < ngrp) store_pair(orsrc, obase, soff, v);
-          else if (ga < ngrp) store_first(orsrc, obase, soff, v);  // the chunk's last whole group
+          if (ga + 1 < ngrp) store_pair<kPolicy>(orsrc, obase, soff, v);
+          else if (ga < ngrp) store_first<kPolicy>(orsrc, obase, soff, v);  // the chunk's last whole group
         }
       }
     }
@@ -1715,7 +1724,7 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
 // onwards, one per lane (tid = threadIdx.x); S.lut holds the code -> symbol
 // LUT.  Returns true in a lane whose chunk is corrupt (or whose index
 // entries are inconsistent).
-template <int kBits>
+template <int kBits, int kPolicy>
 __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, uint64_t total,
                              const uint64_t* __restrict__ index_p, uint32_t log2_chunk, uint64_t n,
                              uint8_t* __restrict__ out_p, uint64_t grp, uint32_t sh_lo,
@@ -1795,10 +1804,10 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
     // Waves whose 64 chunks are all whole and valid are all but at most the
     // last of a valid stream.
     if (__all(live && my_groups == (C >> 3)))
-      decode_wave<kBits, false>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
+      decode_wave<kBits, false, kPolicy>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
                                 my_groups, balance);
     else
-      decode_wave<kBits, true>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
+      decode_wave<kBits, true, kPolicy>(L, T, S, tid, rsrc, orsrc, log2_chunk, sh_lo, sh_hi,
                                my_groups, balance);
     L.arrive(T, S.ring);
     // the position, in 64 bits (a lane that decoded no group is where it began)
@@ -1832,7 +1841,7 @@ __device__ __forceinline__ bool decode_block(const uint8_t* __restrict__ bits, u
   return bad;
 }
 
-template <int kBits>
+template <int kBits, int kPolicy>
 __global__ __launch_bounds__(kDecThreads) void k_decode(
     const uint8_t* __restrict__ bits, const uint64_t* __restrict__ total_p,
     const uint64_t* __restrict__ index, uint32_t log2_chunk,
@@ -1849,7 +1858,7 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
   __syncthreads();
   // a table of another alphabet is refused (nothing decoded)
   if (table_ok) {
-    const bool bad = decode_block<kBits>(bits, *total_p, index, log2_chunk, n, out, blockIdx.x,
+    const bool bad = decode_block<kBits, kPolicy>(bits, *total_p, index, log2_chunk, n, out, blockIdx.x,
                                          sh_lo, sh_hi, S, tid, balance);
     set_error_wave(&hdr->dec_err, QLC_ERR_CORRUPT_STREAM, bad);
   } else if (tid == 0) {
@@ -2637,7 +2646,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
           __builtin_amdgcn_readfirstlane(js[k].split)
               ? split_block<kBits, 6>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                    jb.out, unit, nullptr, L, S.split, opaque_tid())
-              : decode_block<kBits>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
+              : decode_block<kBits, kBits == 6 ? 0 : kStream>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                     jb.out, unit, L.sh_lo, L.sh_hi, S.lane, opaque_tid(), false);
       set_error_wave(jb.err, QLC_ERR_CORRUPT_STREAM, bad);
     } else if (tid == 0) {
@@ -2721,6 +2730,18 @@ hipError_t launch_segment_bits(const uint8_t* in, uint64_t n, uint32_t bits,
   return hipGetLastError();
 }
 
+// A run of 6-bit symbols is 96 bytes, parts of two cache lines that the
+// chunk's neighbouring batches complete.  Non-temporal parts are joined as
+// long as the output is small enough to lie in the memory-side cache, and
+// reach memory one by one beyond (e3m2, non-temporal / normal stores, us: 48
+// Mi symbols at C = 512 31.7 / 34.7, 56 Mi 36.5 / 35.5, 64 Mi 41.8 / 37.1;
+// 2^28 at C = 2048 175 / 125; 32 Mi at C = 1024 40.2 / 42.4).  At C = 256 a
+// chunk is two batches, microseconds apart, and its parts meet at any size
+// (64 Mi 39.8 / 41.6, 2^28 135 / 150).
+static bool stream_six_bit_runs(uint64_t n, uint32_t log2_chunk) {
+  return log2_chunk == 8 || packed_bytes(n, 6) <= (40ull << 20);
+}
+
 hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const uint64_t* index,
                          uint32_t log2_chunk, const qlc_table* table, uint64_t n, uint32_t bits,
                          uint8_t* out, uint32_t* err_out, WsHeader* hdr, hipStream_t stream) {
@@ -2729,8 +2750,14 @@ hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const ui
   if (blocks < 1) blocks = 1;
   // two workgroups fit a compute unit; fewer leave nothing to balance
   const bool balance = blocks > 256 && blocks <= 512;
-  QLC_LAUNCH_BITS(bits, k_decode, dim3((uint32_t)blocks), dim3(kDecThreads), bits_in, total,
-                  index, log2_chunk, table, n, out, err_out, hdr, balance);
+#define QLC_LAUNCH_LANE(B, P)                                                                    \
+  hipLaunchKernelGGL((k_decode<B, P>), dim3((uint32_t)blocks), dim3(kDecThreads), 0, stream,     \
+                     bits_in, total, index, log2_chunk, table, n, out, err_out, hdr, balance)
+  if (bits == 8) QLC_LAUNCH_LANE(8, kStream);
+  else if (bits == 4) QLC_LAUNCH_LANE(4, kStream);
+  else if (stream_six_bit_runs(n, log2_chunk)) QLC_LAUNCH_LANE(6, kStream);
+  else QLC_LAUNCH_LANE(6, 0);
+#undef QLC_LAUNCH_LANE
   return hipGetLastError();
 }
 
