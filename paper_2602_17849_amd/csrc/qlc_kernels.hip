@@ -1593,13 +1593,9 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
 // current chain, so its LDS latency overlaps the current group's LUT
 // gathers and packing.
 //
-// Refill, every eight groups: what was requested eight groups ago goes to
-// the ring and the next superblock is requested, one per lane, which keeps
-// up with 8 bits per symbol.  Every four groups, a wave one of whose lanes'
-// ring does not reach as far as four groups' windows can (kReach, 11-bit
-// codes) takes what is in flight at once, and a lane still short after that
-// gets further superblocks.  The slot a request overwrites lies behind q,
-// since F < q + 3 superblocks.
+// Refill: lane_refill every eight groups and, where codes run long, lane_mid
+// in between.  The slot a request overwrites lies behind q, since F < q + 3
+// superblocks.
 //
 // Output: a batch's pairs change owner through the wave's stage, 16 lanes'
 // runs at a time: lane l of a store holds pair l % 8 of chunk l / 8
@@ -1655,12 +1651,6 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
     OUT = pack_group<kBits>(e, kPart ? eb : L.errbits);                          \
     if (kPart) L.errbits |= keep ? eb : 0u;                                      \
   }
-#define QLC_DEC_REFILL     \
-  {                        \
-    wave.arrive();         \
-    lane_reach(L, wave);   \
-    wave.request();        \
-  }
 #pragma unroll 1
   for (uint32_t g0 = 0; g0 < wave_groups; g0 += R) {
     if (balance) {
@@ -1679,13 +1669,13 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
       QLC_DEC_GROUP(2 * u + 1, b, {})
       pr[u] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 2, a, {})
-      QLC_DEC_GROUP(2 * u + 3, b, lane_reach(L, wave))
+      QLC_DEC_GROUP(2 * u + 3, b, lane_mid(L, wave))
       pr[u + 1] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 4, a, {})
       QLC_DEC_GROUP(2 * u + 5, b, {})
       pr[u + 2] = PairOf<kBits>::make(a, b);
       QLC_DEC_GROUP(2 * u + 6, a, {})
-      QLC_DEC_GROUP(2 * u + 7, b, QLC_DEC_REFILL)
+      QLC_DEC_GROUP(2 * u + 7, b, lane_refill(L, wave))
       pr[u + 3] = PairOf<kBits>::make(a, b);
     }
 #pragma unroll
@@ -1717,7 +1707,6 @@ __device__ __forceinline__ void decode_wave(DecLane& L, Refill& T, DecSmem& S, u
     __builtin_amdgcn_wave_barrier();
   }
 #undef QLC_DEC_GROUP
-#undef QLC_DEC_REFILL
 }
 
 // Decode chunk group `grp` of an n-symbol stream: chunks kDecThreads*grp

@@ -27,27 +27,35 @@ struct Wave {                   // one lane; what a slot of the ring holds
   uint64_t* slot;               // absolute first bit of its superblock
   uint64_t* flight;             // requested, not arrived (~0: nothing)
   uint32_t* polls;              // turns of the loop for one refill
+  uint32_t* group;              // groups decoded, now and at the last request
+  bool* waited;                 // for a superblock asked for less than four groups ago
   bool any(bool b) const { return b && ++*polls < 100; }
   void arrive() const {
-    if (*flight != ~0ull) slot[(*flight >> kSbLog2Bits) & 3] = *flight;
+    if (*flight != ~0ull) {
+      slot[(*flight >> kSbLog2Bits) & 3] = *flight;
+      *waited |= group[0] < group[1] + 4;
+    }
     *flight = ~0ull;
     L.arrived();
   }
   void request() const {
     const bool need = L.wants();
     if (need) *flight = rel0 + 8ull * L.load_offset();
+    group[1] = group[0];
     L.requested(need);
   }
 };
 
 // Codes of len[k % nlen] bits from pos0 on.  0: every window was served;
 // 1: a refill that does not end; 2: a bit missing from the ring; 3: a load
-// offset past the limit; 4: the position is not the sum of the lengths.
+// offset past the limit; 4: the position is not the sum of the lengths; 5: a
+// wait for a superblock that was asked for less than four groups ago.
 extern "C" int walk(uint64_t rel0, uint64_t pos0, uint64_t end, uint32_t groups,
                     const uint8_t* len, uint32_t nlen) {
   LanePos L;
   uint64_t slot[4] = {~0ull, ~0ull, ~0ull, ~0ull}, flight = ~0ull;
-  uint32_t polls = 0;
+  uint32_t polls = 0, group[2] = {0, 0};
+  bool waited = false;
   L.start(true, rel0, pos0, end);
   for (int s = 0; s < 2; ++s) {
     const uint64_t a = rel0 + 8ull * L.load_offset();
@@ -55,7 +63,7 @@ extern "C" int walk(uint64_t rel0, uint64_t pos0, uint64_t end, uint32_t groups,
     L.requested(true);
   }
   L.arrived();
-  const Wave w{L, rel0, slot, &flight, &polls};
+  const Wave w{L, rel0, slot, &flight, &polls, group, &waited};
   w.request();
   uint64_t pos = pos0;
   uint32_t k = 0;
@@ -69,12 +77,10 @@ extern "C" int walk(uint64_t rel0, uint64_t pos0, uint64_t end, uint32_t groups,
     pos += adv;
     if (L.base(rel0) + L.q + 1 != pos) return 4;
     polls = 0;
-    if ((g & 7) == 3) lane_reach(L, w);
-    if ((g & 7) == 7) {
-      w.arrive();
-      lane_reach(L, w);
-      w.request();
-    }
+    group[0] = g + 1;
+    if ((g & 7) == 3) lane_mid(L, w);
+    if ((g & 7) == 7) lane_refill(L, w);
+    if (waited) return 5;
     if (polls >= 100) return 1;
     if (L.load_offset() >= kOobOffset) return 3;
   }
