@@ -2600,7 +2600,7 @@ static_assert(offsetof(DecSmem, lut) == 0 && offsetof(SplitSmem<6>, lut) == 0, "
 static_assert(kSplitThreads == kDecThreads, "one block size");
 static_assert(sizeof(SplitSmem<6>) <= offsetof(DecSmem, ring) + 4 * kStageBase, "the ticket's word");
 
-template <int kBits>
+template <int kBits, int kPolicy>
 __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
     const qlc_job* __restrict__ jobs, uint32_t log2_chunk, BatchHeader* __restrict__ hdr,
     const BatchJobState* __restrict__ js, const uint32_t* __restrict__ grp_job) {
@@ -2635,7 +2635,7 @@ __global__ __launch_bounds__(kDecThreads, 2) void k_decode_batched(
           __builtin_amdgcn_readfirstlane(js[k].split)
               ? split_block<kBits, 6>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                    jb.out, unit, nullptr, L, S.split, opaque_tid())
-              : decode_block<kBits, kBits == 6 ? 0 : kStream>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
+              : decode_block<kBits, kPolicy>(jb.bits, *jb.total_bits, jb.chunk_index, log2_chunk, jb.n,
                                     jb.out, unit, L.sh_lo, L.sh_hi, S.lane, opaque_tid(), false);
       set_error_wave(jb.err, QLC_ERR_CORRUPT_STREAM, bad);
     } else if (tid == 0) {
@@ -2806,15 +2806,22 @@ hipError_t launch_encode_batched(const qlc_job* jobs, uint32_t bits, uint32_t mo
 hipError_t launch_decode_batched(const qlc_job* jobs, uint32_t bits, uint32_t log2_chunk,
                                  BatchHeader* hdr, const BatchJobState* js,
                                  const uint32_t* grp_job, uint32_t grid, hipStream_t stream) {
-  QLC_LAUNCH_BITS(bits, k_decode_batched, dim3(grid), dim3(kDecThreads), jobs, log2_chunk, hdr,
-                  js, grp_job);
+#define QLC_LAUNCH_BATCH(B, P)                                                            \
+  hipLaunchKernelGGL((k_decode_batched<B, P>), dim3(grid), dim3(kDecThreads), 0, stream,  \
+                     jobs, log2_chunk, hdr, js, grp_job)
+  if (bits == 8) QLC_LAUNCH_BATCH(8, kStream);
+  else if (bits == 4) QLC_LAUNCH_BATCH(4, kStream);
+  else if (log2_chunk == 8) QLC_LAUNCH_BATCH(6, kStream);  // (as stream_six_bit_runs; the
+  else QLC_LAUNCH_BATCH(6, 0);                             // host does not know the sizes)
+#undef QLC_LAUNCH_BATCH
   return hipGetLastError();
 }
 
 int batched_blocks_per_cu(bool decode) {
   int nb = 0;
   hipError_t e = decode ? hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                              &nb, reinterpret_cast<const void*>(k_decode_batched<8>), kDecThreads, 0)
+                              &nb, reinterpret_cast<const void*>(k_decode_batched<8, kStream>), kDecThreads,
+                              0)
                         : hipOccupancyMaxActiveBlocksPerMultiprocessor(
                               &nb, reinterpret_cast<const void*>(k_encode_batched<8>), kEncThreads, 0);
   return (e == hipSuccess && nb > 0) ? nb : 1;
