@@ -408,7 +408,7 @@ qlc_status qlc_decode_ex(const uint8_t* bits, const uint64_t* total_bits,
     return hip_status(launch_decode_split(bits, total_bits, chunk_index, log2c, table, n,
                                           symbol_bits, out, err_out, v.hdr, stream));
   return hip_status(launch_decode(bits, total_bits, chunk_index, log2c, table, n, symbol_bits, out,
-                                  err_out, v.hdr, stream));
+                                  err_out, v.hdr, (uint32_t)device_info().cus, stream));
 }
 
 qlc_status qlc_decode_sym(const uint8_t* bits, const uint64_t* total_bits,

@@ -23,9 +23,11 @@ hipError_t launch_encode(const uint8_t* in, uint64_t n, uint32_t bits, const qlc
                          hipStream_t stream);
 hipError_t launch_segment_bits(const uint8_t* in, uint64_t n, uint32_t bits,
                                const qlc_table* table, uint64_t* seg_bits, hipStream_t stream);
+// cus: the device's compute units.
 hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const uint64_t* index,
                          uint32_t log2_chunk, const qlc_table* table, uint64_t n, uint32_t bits,
-                         uint8_t* out, uint32_t* err_out, WsHeader* hdr, hipStream_t stream);
+                         uint8_t* out, uint32_t* err_out, WsHeader* hdr, uint32_t cus,
+                         hipStream_t stream);
 // Several lanes per chunk (log2_chunk <= kSplitMaxLog2Chunk).
 constexpr uint32_t kSplitMaxLog2Chunk = 14;
 constexpr uint32_t kSplitUnitLog2 = 14;  // symbols per split unit (one workgroup)

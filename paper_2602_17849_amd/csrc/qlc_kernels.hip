@@ -1601,12 +1601,11 @@ __device__ __forceinline__ void build_dec_lut(const qlc_table* __restrict__ tabl
 // runs at a time: lane l of a store holds pair l % 8 of chunk l / 8
 // (+ kRuns per store).
 //
-// balance: the launch fits the device at once, so that a wave's end is the
-// kernel's.  The older of the two waves of a SIMD wins every cycle both
-// want, ends first and leaves the other to run alone at little more than
-// half the pair's rate; with a priority that falls with each quarter of the
-// chunk the two end together (256 MiB, C = 2048: 134 -> 130 us; a queue of
-// many groups per workgroup loses 7 % by it).
+// balance (lane_balance): the launch fits the device at once, so that a
+// wave's end is the kernel's.  The older of the two waves of a SIMD wins
+// every cycle both want, ends first and leaves the other to run alone at
+// little more than half the pair's rate; with a priority that falls with
+// each quarter of the chunk the two end together.
 //
 // kPolicy: cache policy of the stored runs, kStream but for many 6-bit
 // symbols (stream_six_bit_runs).
@@ -2733,12 +2732,12 @@ static bool stream_six_bit_runs(uint64_t n, uint32_t log2_chunk) {
 
 hipError_t launch_decode(const uint8_t* bits_in, const uint64_t* total, const uint64_t* index,
                          uint32_t log2_chunk, const qlc_table* table, uint64_t n, uint32_t bits,
-                         uint8_t* out, uint32_t* err_out, WsHeader* hdr, hipStream_t stream) {
+                         uint8_t* out, uint32_t* err_out, WsHeader* hdr, uint32_t cus,
+                         hipStream_t stream) {
   const uint64_t nchunks = (n + (1ull << log2_chunk) - 1) >> log2_chunk;
   uint64_t blocks = (nchunks + kDecThreads - 1) / kDecThreads;
   if (blocks < 1) blocks = 1;
-  // two workgroups fit a compute unit; fewer leave nothing to balance
-  const bool balance = blocks > 256 && blocks <= 512;
+  const bool balance = lane_balance(blocks, cus);
 #define QLC_LAUNCH_LANE(B, P)                                                                    \
   hipLaunchKernelGGL((k_decode<B, P>), dim3((uint32_t)blocks), dim3(kDecThreads), 0, stream,     \
                      bits_in, total, index, log2_chunk, table, n, out, err_out, hdr, balance)

@@ -87,6 +87,7 @@ extern "C" int walk(uint64_t rel0, uint64_t pos0, uint64_t end, uint32_t groups,
   return 0;
 }
 extern "C" uint64_t max_lane_sb() { return kMaxLaneSb; }
+extern "C" bool balance(uint64_t blocks, uint32_t cus) { return lane_balance(blocks, cus); }
 """
 
 
@@ -106,6 +107,8 @@ def walk(tmp_path_factory):
         b = bytes(int(v) for v in lens)
         return lib.walk(rel0, pos0, end, groups, b, len(b))
     run.max_sb = lib.max_lane_sb()
+    lib.balance.argtypes, lib.balance.restype = [u64, u32], ctypes.c_bool
+    run.balance = lib.balance
     return run
 
 
@@ -165,3 +168,11 @@ def test_random_entries(walk):
         pos0 = int(rng.integers(0, 1 << 35)) % (walk.max_sb << 9)
         end = pos0 + int(rng.integers(0, 1 << 36))
         assert walk(0, pos0, end, 32, lens) == 0
+
+
+@pytest.mark.parametrize("cus", [32, 64, 256, 304])
+def test_balanced_launches(walk, cus):
+    """Only launches that fit the device at once, whatever its size."""
+    assert not walk.balance(1, cus) and not walk.balance(cus, cus)
+    assert walk.balance(cus + 1, cus) and walk.balance(2 * cus, cus)
+    assert not walk.balance(2 * cus + 1, cus) and not walk.balance(1 << 33, cus)
