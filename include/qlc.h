@@ -258,11 +258,12 @@ qlc_status qlc_decode(const uint8_t* bits, const uint64_t* total_bits,
  *                      guessed start, the lanes correct their starts from
  *                      their neighbours' exits, then each decodes about 64
  *                      (32) codes; latency for tensors of few chunks;
- *   QLC_DECODER_AUTO   the one qlc_decode / qlc_decode_sym use: the decoder
- *                      with the shorter estimated time, from models of both
- *                      fitted on MI355X (256 Mi down to 64 Ki symbols):
- *                      LANE  max(5.2 us + 33.1 ns * C, 5 us + 0.62 ps * n),
- *                      SPLIT 9.5 us + 1.0 ps * n (only for C <= 16384).
+ *   QLC_DECODER_AUTO   the one qlc_decode / qlc_decode_sym use: SPLIT up to
+ *                      about 29,700 * C - 5.4 million symbols (C <= 16384), where
+ *                      it is ahead on MI355X by 10 % and more on ordinary
+ *                      data; beyond, LANE, whose time does not depend on the
+ *                      data (SPLIT takes several times as long for tensors
+ *                      that are nearly all one value).
  * symbol_bits as in the *_sym entry points below (8 for bytes); other
  * arguments and errors as qlc_decode. */
 typedef enum qlc_decoder {

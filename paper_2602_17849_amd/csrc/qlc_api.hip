@@ -362,20 +362,24 @@ qlc_status qlc_compress_noalloc(const uint8_t* in, uint64_t n, qlc_layout_mode m
                       chunk_index_out, total_bits_out, err_out, ws, kStaticWsBytes, stream);
 }
 
-// The decoder with the shorter estimated time (ns), from two-term models
-// fitted to measured decode times on MI355X (64 Ki to 256 Mi symbols, C =
-// 256 to 8192): one lane per chunk walks C codes in sequence (a fixed cost
-// plus 33.1 ns per code; C = 256 13.7 us, 2048 72 us) unless the chunks fill
-// the device, where it takes 0.62 ps per symbol (64 Mi symbols at C = 256:
-// 46.5 us); the split decoder costs 9.5 us plus 1.0 ps per symbol (1 Mi
-// symbols 10.1 us, 9 Mi 18.3, 64 Mi 75).
+// The split decoder takes 9.5 us plus 1.0 ps per symbol of ordinary data (1
+// Mi symbols 10.1 us, 9 Mi 17.4, 64 Mi 75 on MI355X), but up to ten times
+// that where codes of one length fill whole pieces of a chunk: a lane that
+// starts between two codes then never falls in step, and the pieces of a
+// chunk are put right one after another.  One lane per chunk walks C codes
+// whatever they are (5.2 us plus 33.1 ns per code; 5 us plus 0.62 ps per
+// symbol once the chunks fill the device).  Up to the line, n < 29,700 C -
+// 5.4 million, ordinary data decodes so much faster in pieces that it is
+// taken.  Beyond it the lead on ordinary data is 10-15 % and gone within
+// another 15 % of n, and tensors of nearly nothing but zeros would pay for it
+// many times over.  Split and lane, us, at 12 Mi symbols, C = 512: e4m3 20.3
+// and 23.0, 3 % not zero 33 and 22, all zero 34 and 22; 56 Mi, C = 2048: 65
+// and 73, 143 and 71, 385 and 68; 112 Mi, C = 4096: 119 and 139, 275 and 138,
+// 1422 and 129.
 static qlc_decoder auto_decoder(uint64_t n, uint32_t log2c) {
   if (log2c > kSplitMaxLog2Chunk) return QLC_DECODER_LANE;
   const uint64_t C = 1ull << log2c;
-  const uint64_t lane_walk = 5200 + C * 331 / 10, lane_rate = 5000 + n * 62 / 100000;
-  const uint64_t lane = lane_walk > lane_rate ? lane_walk : lane_rate;
-  const uint64_t split = 9500 + n / 1000;
-  return split < lane ? QLC_DECODER_SPLIT : QLC_DECODER_LANE;
+  return n * 1235 / 1000000 + 6700 < C * 367 / 10 ? QLC_DECODER_SPLIT : QLC_DECODER_LANE;
 }
 
 qlc_decoder qlc_decoder_choice(uint64_t n, uint32_t chunk_symbols) {
