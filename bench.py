@@ -34,7 +34,8 @@ WORKLOAD = ("single 256 MiB e4m3 tensor 8192x32768: FP32 Laplace(0,1), 1% rows x
             "block-32 power-of-two scale, RNE e4m3; per-tensor SEARCH_QUAD table; seed 1")
 KERNEL_SOURCES = ["paper_2602_17849_amd/csrc/qlc_kernels.hip",
                   "paper_2602_17849_amd/csrc/qlc_device.h",
-                  "paper_2602_17849_amd/csrc/qlc_internal.h"]
+                  "paper_2602_17849_amd/csrc/qlc_internal.h",
+                  "paper_2602_17849_amd/csrc/qlc_lane_pos.h"]
 
 
 def kernel_source_hash() -> str:

@@ -144,14 +144,20 @@ __host__ __device__ inline uint32_t batch_auto_log2_seg(uint64_t T) {
   return l < kBatchMinLog2Seg ? kBatchMinLog2Seg : l > kBatchAutoMaxLog2Seg ? kBatchAutoMaxLog2Seg : l;
 }
 
-// Decode (QLC_DECODER_AUTO): every job in split units when a time model of
-// the two decoders, fitted to batched decodes on MI355X, favours the split
-// one for T symbols at chunk size C = 2^log2c (C <= 16384): split about
-// 26 us + 2.5 ps per symbol (two workgroups of 256 lanes per CU on 2^14-
-// symbol units), one lane per chunk at least 19.4 us + 44 ns per code of a
-// chunk (a lane walks its chunk alone) and 0.46 ps per symbol once the
-// device is full.  Otherwise only jobs of fewer chunks than a lane group
-// holds are split.
+// Decode (QLC_DECODER_AUTO): every job in split units where a time model of
+// the two decoders favours the split one for T symbols at chunk size C =
+// 2^log2c (C <= 16384); otherwise only jobs of fewer chunks than a lane group
+// holds.  The model was fitted to batched decodes with earlier, slower forms
+// of both (split 26 us + 2.5 ps per symbol in units of 2^14 symbols; one lane
+// per chunk at least 19.4 us + 44 ns per code of a chunk, and 0.46 ps per
+// symbol once the device is full).  Both are a fifth to a half faster now, and
+// the line between them still lies where it should at nearly all sizes
+// measured (split and lane, us, e4m3, MI355X): one job of 4 Mi symbols at C = 512 24.3
+// and 29.1, of 16 Mi 61.0 and 33.2; 64 jobs of 256 Ki 36.4 and 30.1, of 1 Mi
+// at C = 2048 103 and 86; one of 16 Mi 60.9 and 83.8.  Only 8 Mi symbols at
+// C = 512 get the slower one, 29.0 for 25.4.  (Tensors of nearly one value
+// take the split units several times as long, which is why the line is not
+// moved up with the split decoder's speed.)
 __host__ __device__ inline bool batch_split_all(uint64_t T, uint32_t log2c) {
   if (log2c > 14 || T > (1ull << 40)) return false;
   const uint64_t split_ns = 26000 + T * 25 / 10000;

@@ -26,13 +26,21 @@ __device__ __forceinline__ uint4 gload_u4(const QLC_GLOBAL GVec4* p, uint64_t i)
   return make_uint4(v.x, v.y, v.z, v.w);
 }
 
-// Cache policy (non-temporal) of the stores of a large output, which is
-// written once and read by nothing of the same call.  Stored normally it
-// stays dirty in the caches and is written back line by line when the next
-// pass's reads push it out.  At 2^28 symbols compress 189 -> 167 us (its
-// histogram pass read 3.4 TB/s in a row of calls, 5.3 in the first one),
-// decode 124 -> 121; 48 Mi symbols encoded with a given table 38.0 -> 36.3;
-// 9 Mi and less unchanged.  (Non-temporal reads are slower: the decoder's
+// Cache policy (non-temporal) of the encoders' streams and of the lane
+// decoder's output (the split decoder stores normally, and 6-bit runs of
+// large tensors too: stream_six_bit_runs).  They are written once and read by
+// nothing of the same call.  Stored normally they stay dirty in the caches and
+// are written back line by line when the next pass's reads push them out.  At
+// 2^28 symbols compress 189 -> 167 us (its histogram pass read 3.4 TB/s in a
+// row of calls, 5.3 in the first one), decode 124 -> 121; 48 Mi symbols
+// encoded with a given table 38.0 -> 36.3; 9 Mi and less unchanged, so the
+// policy has no size of its own.  What reads the result next finds less of it
+// in the caches.  Normal stores against these, us for both calls together, at
+// 1 / 16 / 64 Mi and 2^28 symbols: compress and decode 28.6 / 62.3 / 134.7 /
+// 307 and 28.7 / 61.8 / 135.1 / 286; decode and a read of the output 20.0 /
+// 38.6 / 93.3 / 174.6 and 20.5 / 38.6 / 94.4 / 173.1; compress and a copy of
+// the stream 20.4 / 40.6 / 79.9 / 286 and 20.8 / 41.7 / 82.4 / 278.
+// (Non-temporal reads are slower: the decoder's
 // 64-byte pieces lose the other half of a line, 121 -> 157 us, and the
 // encoder's second pass misses what its first one left, 36.3 -> 38.6.)
 constexpr int kStream = 2;
@@ -189,7 +197,8 @@ __device__ __forceinline__ void build_table_block(const uint64_t* h_in, uint32_t
   // The layout candidates: four per thread and step.  The first step's are
   // loaded before anything else (1308 of 512 threads' quad search: all of
   // them), so that their latency passes behind the ranking instead of
-  // between the prefix sums and the costs (search 2.2 -> 1.1 us).
+  // between the prefix sums and the costs (costs and argmin 2.2 -> 1.5 us;
+  // histogram and table of 1 Mi symbols 10.2 -> 9.7).
   const uint32_t na = mode_areas(mode);
   const uint32_t max_distinct = mode == QLC_LAYOUT_SEARCH_QUAD ? 4u
                                 : (mode >= 17u && mode <= 24u) ? mode - 16u : 8u;
@@ -1130,8 +1139,8 @@ __global__ __launch_bounds__(kEncThreads) void k_encode(
 // LUT is re-indexed by the whole code word: because widths never decrease,
 // the codes of area a occupy the integer range [a << w_a, (a + 1) << w_a)
 // and these ranges are disjoint, so a 2048-entry LDS table maps code ->
-// symbol (16-bit entries: the top bit marks an invalid suffix).  The per-symbol chain is pure
-// VALU: the 3-bit area code selects the shift 29 - w_a from an 8-byte
+// symbol (16-bit entries: the top bit marks an invalid suffix).  The
+// per-symbol chain is pure VALU: the 3-bit area code selects the shift 29 - w_a from an 8-byte
 // register table (v_perm), the code is the window shifted right by it, and
 // three funnel shifts advance a 96-bit window by 3 + w_a bits.
 //
@@ -1144,10 +1153,10 @@ __global__ __launch_bounds__(kEncThreads) void k_encode(
 // wave decodes a group of 8 symbols in 610 cycles, its ~97 instructions at
 // 5-6 cycles each whatever they are; the pair takes about 450 per group and
 // wave.  With the loads and stores left out the kernel takes 110 us of its
-// 125: it is bound by its instruction stream, then by the memory system's
-// answer to 131,072 streams.  256 MiB 152 -> 125.5 us (4.0 TB/s of stream
-// and output); 48 shards of 1-32 MiB in one call 384 -> 315 us; one wave per
-// SIMD (32 Mi 6-bit symbols, C = 1024) 47.9 -> 46.5 us.
+// 122: it is bound by its instruction stream, then by the memory system's
+// answer to 131,072 streams.  256 MiB 152 -> 122 us (4.1 TB/s of stream
+// and output); 48 shards of 1-32 MiB in one call 383 -> 307 us; one wave per
+// SIMD (32 Mi 6-bit symbols, C = 1024) 47.9 -> 40.2 us.
 // ===========================================================================
 constexpr int kDecLanes = kDecThreads;     // chunks per workgroup
 constexpr int kRingWords = kRingBits / 32 + 3;  // the ring and 3 mirror words
@@ -1890,8 +1899,10 @@ __global__ __launch_bounds__(kDecThreads) void k_decode(
 //      at a time, until the two meet, it cost the few workgroups that have
 //      such a lane 3.5 us).  After round r the
 //      first r + 1 lanes of every chunk are exact; the rounds stop when no
-//      lane's exit changed, so after at most G + 1 rounds, and in practice
-//      one round suffices;
+//      lane's exit changed, so after at most G + 1 rounds.  One suffices in
+//      practice, unless codes of one length fill whole pieces (a tensor of
+//      nearly one value): such walks never fall in step, and every round
+//      makes one more lane exact;
 //   4. a scan of the code counts gives every lane the position of its first
 //      symbol; the lane decodes its codes through the code-word LUT into an
 //      LDS copy of the workgroup's output, which is then stored with
